@@ -108,6 +108,9 @@ typedef struct lbm_lattice lbm_lattice;
  * lattice size so that three (FP32), four (FP16, BF16) or two (FP64)
  * workgroups per compute unit cover the lattice in one round, at least 8:
  * 92, 69, 69, 137 rows on 4096^2); a smaller one with {0, 64, 4, 1, 1, 0}).
+ * Until a shape is set by hand, lbm_step takes register tiles of its own
+ * choice in its place on lattices of at most 3 * 2^21 cells: workgroups that
+ * hold a tile of the lattice in registers for up to nine steps.
  *   variant   0 = one cell per lane (nine direct loads),
  *             1, 2, 3 = 2, 4, 8 consecutive cells per lane (aligned vector
  *             loads, x-shift by cross-lane exchange; needs nx % 2^variant == 0
@@ -209,7 +212,9 @@ LBM_API lbm_status lbm_init_equilibrium(lbm_lattice *lat, const double *rho, con
  * steps in one launch of the same shape with r steps per pass (variant
  * 6 + r) when r >= 2 and that shape is supported (for a shared-halo shape
  * with r < 4: the same with one wave per strip and flags 2), else r one-step
- * launches; every split gives bit-identical results. */
+ * launches.  With register tiles (see lbm_launch) and n > 1: the least number
+ * of tile launches, of nearly equal step counts.  Every split gives
+ * bit-identical results. */
 LBM_API lbm_status lbm_step(lbm_lattice *lat, int64_t n);
 /* Kernel launches lbm_step(lat, n) makes with the current shapes; -1 if
  * lat is NULL or n < 0. */
@@ -292,7 +297,8 @@ LBM_API lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg);
 /* Times the supported launch shapes on this lattice (reps launches each,
  * the state is left unchanged) and selects the one with the least time per
  * step; the fastest one-step shape is kept for a single left-over step
- * (see lbm_step for the rest).  best_us
+ * (see lbm_step for the rest).  Register tiles stay in use where they take
+ * less time per step than the selected shape.  best_us
  * receives microseconds per step.  best/best_us may be NULL.  Syncs. */
 LBM_API lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *best_us);
 /* Times n launches of the current shape (state unchanged; syncs); avg_us is

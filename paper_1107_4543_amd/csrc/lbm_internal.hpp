@@ -43,6 +43,15 @@ int multi_strip_cols(int T, int elem_bytes, int lanes = 64);
 
 hipError_t launch_step(const View &v, const void *src, void *dst, const lbm_launch &cfg,
                        hipStream_t st);
+
+// Shape of the register-tile step kernel: workgroups of `waves` waves, `rows`
+// rows per lane, up to `steps` steps per launch (0: not used).
+struct TileShape {
+    int32_t rows, waves, steps;
+};
+bool tile_fits(const View &v);
+TileShape tile_shape(const View &v);
+hipError_t launch_tile(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st);
 // measure_only: compute max |g| (before scaling) into result[0], store nothing.
 hipError_t launch_init(const View &v, const double *rho, const double *ux, const double *uy,
                        void *dst, double *partials, double *result, bool measure_only,
@@ -166,5 +175,6 @@ struct lbm_lattice {
     bool initialized = false;
     lbm_launch launch{};
     lbm_launch single{};       // one-step shape for the steps a multi-step shape leaves over
+    lbm::TileShape tile{};     // register tiles lbm_step takes in place of `launch` (steps 0: none)
     lbm_pool *pool = nullptr;  // non-NULL while a pool advances this lattice
 };

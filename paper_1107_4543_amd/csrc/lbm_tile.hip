@@ -1,0 +1,335 @@
+// Several steps per launch on register tiles: the step kernel of small and
+// medium lattices.
+//
+// A workgroup of W waves holds a tile of 64 columns by W R rows in registers
+// (lane = column, wave = R consecutive rows), advances it T steps and writes
+// the cells that T steps leave valid: the tile without T - 1 rows and columns
+// on each side.  Populations move along x by DPP whole-wave shifts and along
+// y by register renaming; only the rows at a wave's edge go through LDS (six
+// values per lane and step, two buffers in turn, one barrier per step).  A
+// wave skips the steps in which none of its rows is needed any more, so half
+// of the halo rows' work is saved.
+//
+// Why tiles: below about 2^22 cells the strips of k_step_multi are too few to
+// fill the device with segments tall enough to pay for their 2 (T-1) start-up
+// rows, and one-step launches spend most of their 2.8 us on launch and memory
+// latency.  A tile launch costs about 3.3 us plus 0.3 us per step until the
+// vector ALUs fill; from there on it issues close to the ALU's rate, and what
+// bounds it is the share of the tile that is halo: a 64 x 48 tile
+// writes 52 x 36 cells after T = 7 steps.  Measured against what these sizes
+// took before (us per step): FP32 64^2 2.8 -> 0.71, 181 x 147 2.9 -> 0.80
+// (both one-step launches), 600 x 430 4.5 -> 1.5, 1000 x 760 5.9 -> 3.1, 2048^2
+// 17.1 -> 13.4 (strips); FP64 64^2 3.2 -> 0.92, 1500 x 1001 14.0 -> 9.8; BF16
+// 600 x 430 3.9 -> 1.7.
+#include <algorithm>
+#include <cmath>
+
+#include "lbm_step_common.hpp"
+
+namespace lbm {
+
+namespace {
+
+template <typename C>
+struct TileArgs {
+    const void *src;
+    void *dst;
+    int32_t nx, ny, pitch, tiles_x;
+    int32_t out_cols, out_rows, nblocks, T;
+    uint32_t inv_tiles_x;     // ceil(2^32 / tiles_x) where that divides exactly, else 0
+    int64_t plane;
+    Relax<C> r;
+    float scale, inv_scale;
+};
+
+// Most waves per workgroup that the registers of R rows per lane leave room for
+// (512 registers per SIMD lane: a wave of the largest workgroup may hold
+// 2048 / waves of them).
+template <typename S, int R>
+constexpr int tile_max_waves()
+{
+    return sizeof(typename Store<S>::wide) == 8 && R > 4 ? 8 : 16;
+}
+
+constexpr int kTileCols = 64;     // columns of a tile: one per lane
+constexpr int kTileXch = kTileCols + 2;   // columns of an exchange row
+
+// Waves that a tile of t needs: fewer than its shape's where the lattice has
+// fewer rows.
+int tile_waves(const TileShape &t, int ny, int steps)
+{
+    const int need = std::min(t.rows * t.waves, ny + 2 * (steps - 1));
+    return (need + t.rows - 1) / t.rows;
+}
+
+size_t tile_lds(int waves, size_t wide) { return (size_t)waves * 2 * 6 * kTileXch * wide; }
+
+// v mod n for v in [-64, n + 64): no division unless n is small.
+__device__ __forceinline__ int wrap_near(int v, int n)
+{
+    if (n < 64) return wrap_mod(v, n);
+    return v < 0 ? v + n : (v >= n ? v - n : v);
+}
+
+// Value of the lane to the left / right; lane 0 / 63 of the wave gets zero
+// (bound_ctrl: the result needs no copy of an old value, so the shift can
+// write any register; those lanes' cells are not used).
+template <int CTRL, typename V>
+__device__ __forceinline__ V shift0(V v)
+{
+    if constexpr (sizeof(V) == 4) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+    } else {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+        return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    }
+}
+template <typename V>
+__device__ __forceinline__ V left(V v) { return shift0<kDppWaveShr1>(v); }
+template <typename V>
+__device__ __forceinline__ V right(V v) { return shift0<kDppWaveShl1>(v); }
+
+template <typename S, typename C, int R>
+__global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(TileArgs<C> a)
+{
+    using Raw = typename Store<S>::raw;
+    using W = typename Store<S>::wide;
+    constexpr uint32_t E = sizeof(Raw);
+    extern __shared__ char lds[];
+    const int lane = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.y), nw = (int)blockDim.y;
+    const int T = a.T;
+    const int bid = remap_xcd((int)blockIdx.x, a.nblocks);
+    const int ty = a.inv_tiles_x ? (int)__umulhi((uint32_t)bid, a.inv_tiles_x) : bid / a.tiles_x;
+    const int tx = bid - ty * a.tiles_x;
+    const int x0 = tx * a.out_cols, y0 = ty * a.out_rows;
+    const int rows = min(a.out_rows, a.ny - y0);          // rows to write
+    const int need = rows + 2 * (T - 1);                  // tile rows they depend on
+    const int lo = wv * R;                                // first tile row of the wave
+    const int xl = x0 + lane - (T - 1);
+    const int c = wrap_near(xl, a.nx);
+    const uint32_t c0 = (uint32_t)c * E;
+    const uint32_t cm = (uint32_t)((c == 0 ? a.nx : c) - 1) * E;
+    const uint32_t cp = (uint32_t)((c + 1 == a.nx) ? 0 : c + 1) * E;
+    const uint32_t pb = (uint32_t)a.plane * E, rb = (uint32_t)a.pitch * E;
+    const __amdgpu_buffer_rsrc_t src = whole_rsrc((const char *)a.src), dst = whole_rsrc((const char *)a.dst);
+    W w[R][9];
+    if (lo < need) {
+        int y = y0 - (T - 1) + lo;
+        y = a.ny < 64 ? __builtin_amdgcn_readfirstlane(wrap_mod(y, a.ny)) : y < 0 ? y + a.ny : y >= a.ny ? y - a.ny : y;
+        int ym = (y == 0 ? a.ny : y) - 1;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int yp = (y + 1 == a.ny) ? 0 : y + 1;
+            const uint32_t r0 = (uint32_t)y * rb, rm = (uint32_t)ym * rb, rp = (uint32_t)yp * rb;
+            w[j][0] = ld_buf<S, false>(src, c0, r0);
+            w[j][1] = ld_buf<S, false>(src, cm, 1 * pb + r0);
+            w[j][2] = ld_buf<S, false>(src, c0, 2 * pb + rm);
+            w[j][3] = ld_buf<S, false>(src, cp, 3 * pb + r0);
+            w[j][4] = ld_buf<S, false>(src, c0, 4 * pb + rp);
+            w[j][5] = ld_buf<S, false>(src, cm, 5 * pb + rm);
+            w[j][6] = ld_buf<S, false>(src, cp, 6 * pb + rm);
+            w[j][7] = ld_buf<S, false>(src, cp, 7 * pb + rp);
+            w[j][8] = ld_buf<S, false>(src, cm, 8 * pb + rp);
+            ym = y;
+            y = yp;
+        }
+    }
+    // rows that cross a wave's edge go through LDS: [wave][step parity][value
+    // (populations 2, 5, 6 of the wave's last row, 4, 7, 8 of its first)]
+    // [column + 1] (the pad makes the neighbouring columns constant offsets)
+    W *const mine = (W *)lds + wv * (2 * 6 * kTileXch) + lane + 1;
+    const W *const below = (W *)lds + (wv > 0 ? wv - 1 : 0) * (2 * 6 * kTileXch) + lane + 1;
+    const W *const above = (W *)lds + (wv + 1 < nw ? wv + 1 : wv) * (2 * 6 * kTileXch) + lane + 1;
+    auto update = [&](int j) {
+        cell_update<S, C>(w[j], a.r, a.scale, a.inv_scale);
+        round_trip9<S>(w[j]);
+    };
+    auto step = [&](int k, auto par) {
+        constexpr int B = decltype(par)::value * 6 * kTileXch;
+        // step k is needed on tile rows k .. need - 1 - k
+        const bool live = lo + R > k && lo < need - k;    // wave-uniform
+        if (live) {
+            update(0);
+            if constexpr (R > 1) update(R - 1);
+            mine[B + 0 * kTileXch] = w[R - 1][2];
+            mine[B + 1 * kTileXch] = w[R - 1][5];
+            mine[B + 2 * kTileXch] = w[R - 1][6];
+            mine[B + 3 * kTileXch] = w[0][4];
+            mine[B + 4 * kTileXch] = w[0][7];
+            mine[B + 5 * kTileXch] = w[0][8];
+#pragma unroll
+            for (int j = 1; j < R - 1; ++j) update(j);
+        }
+        __syncthreads();
+        if (live) {
+            // new row j: populations 0, 1, 3 of old row j, 2, 5, 6 of old row
+            // j - 1, 4, 7, 8 of old row j + 1, shifted along x
+            W n2 = below[B], n5 = below[B + 1 * kTileXch - 1], n6 = below[B + 2 * kTileXch + 1];
+            const W u4 = above[B + 3 * kTileXch], u7 = above[B + 4 * kTileXch + 1], u8 = above[B + 5 * kTileXch - 1];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const W k2 = w[j][2], k5 = w[j][5], k6 = w[j][6];
+                w[j][1] = left(w[j][1]);
+                w[j][3] = right(w[j][3]);
+                w[j][2] = n2;
+                w[j][5] = n5;
+                w[j][6] = n6;
+                if (j + 1 < R) {
+                    w[j][4] = w[j + 1 < R ? j + 1 : j][4];
+                    w[j][7] = right(w[j + 1 < R ? j + 1 : j][7]);
+                    w[j][8] = left(w[j + 1 < R ? j + 1 : j][8]);
+                    n2 = k2;
+                    n5 = left(k5);
+                    n6 = right(k6);
+                } else {
+                    w[j][4] = u4;
+                    w[j][7] = u7;
+                    w[j][8] = u8;
+                }
+            }
+        }
+    };
+    int k = 0;
+    for (; k + 2 < T; k += 2) {
+        step(k, std::integral_constant<int, 0>{});
+        step(k + 1, std::integral_constant<int, 1>{});
+    }
+    if (k + 1 < T) step(k, std::integral_constant<int, 0>{});
+    if (lo + R <= T - 1 || lo >= T - 1 + rows) return;
+    const bool col = lane >= T - 1 && lane < T - 1 + a.out_cols && xl < a.nx;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int tr = lo + j - (T - 1);                  // row of the tile's output
+        if (tr < 0 || tr >= rows) continue;               // wave-uniform
+        cell_update<S, C>(w[j], a.r, a.scale, a.inv_scale);
+        const uint32_t ro = (uint32_t)(y0 + tr) * rb;
+        if (col) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) st_buf<S>(dst, c0, (uint32_t)i * pb + ro, w[j][i]);
+        }
+    }
+}
+
+template <typename S, typename C>
+hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st)
+{
+    TileArgs<C> a;
+    a.src = src;
+    a.dst = dst;
+    a.nx = v.nx;
+    a.ny = v.ny;
+    a.pitch = v.pitch;
+    a.plane = v.plane;
+    a.r = make_relax<C>(v);
+    a.scale = (float)v.scale;
+    a.inv_scale = (float)v.inv_scale;
+    a.T = steps;
+    a.out_cols = kTileCols - 2 * (steps - 1);
+    a.out_rows = t.rows * t.waves - 2 * (steps - 1);
+    if (steps < 1 || a.out_cols < 1 || a.out_rows < 1 || !tile_fits(v)) return hipErrorInvalidValue;
+    a.tiles_x = (v.nx + a.out_cols - 1) / a.out_cols;
+    a.nblocks = a.tiles_x * ((v.ny + a.out_rows - 1) / a.out_rows);
+    const uint64_t inv = (((uint64_t)1 << 32) + a.tiles_x - 1) / a.tiles_x;
+    a.inv_tiles_x = a.tiles_x > 1 && (uint64_t)a.nblocks * a.tiles_x < ((uint64_t)1 << 32) ? (uint32_t)inv : 0;
+    const int waves = tile_waves(t, v.ny, steps);
+    const dim3 grid(a.nblocks), block(64, waves);
+    const size_t lds = tile_lds(waves, sizeof(typename Store<S>::wide));
+#define LBM_TILE(R_)                                                                                      \
+    case R_:                                                                                              \
+        if (waves > tile_max_waves<S, R_>()) return hipErrorInvalidValue;                                 \
+        hipLaunchKernelGGL((k_step_tile<S, C, R_>), grid, block, lds, st, a);                             \
+        break;
+    switch (t.rows) {
+        LBM_TILE(1) LBM_TILE(2) LBM_TILE(3) LBM_TILE(4)
+    default: return hipErrorInvalidValue;
+    }
+#undef LBM_TILE
+    return hipGetLastError();
+}
+
+// Launch time of a tile shape, from measurements of about 17 sizes from 37 x
+// 29 to 2600 x 2400 per storage type (6,000 launches each, residual 4 %; the
+// shape it picks is within 2-3 % of the best one on average).  t0: launch and
+// memory latency; row: one row of one wave, one step, on a SIMD of its own;
+// wg: load and store of one workgroup; bw: bytes per us to and from memory.
+struct TileCost {
+    double t0, row, wg, bw;
+};
+constexpr TileCost kTileCost[4] = {{1.99, 0.205, 1.70, 6.1e6},    // FP64
+                                   {1.89, 0.110, 1.69, 5.1e6},    // FP32
+                                   {1.43, 0.139, 2.11, 3.75e6},   // FP16
+                                   {2.02, 0.134, 1.50, 3.75e6}};  // BF16
+
+double tile_us(const View &v, const TileShape &t)
+{
+    const TileCost &c = kTileCost[v.storage];
+    const int h = t.steps - 1, R = t.rows;
+    const int oc = kTileCols - 2 * h, orow = R * t.waves - 2 * h;
+    if (oc < 8 || orow < 1) return INFINITY;
+    const double nb = (double)((v.nx + oc - 1) / oc) * ((v.ny + orow - 1) / orow);
+    const int need = std::min(orow, v.ny) + 2 * h;
+    int live = 0;                                         // wave-steps of a tile
+    for (int w = 0; w * R < need; ++w) live += std::min(t.steps, std::min(w * R + R, need - w * R));
+    // workgroups resident per compute unit (512 registers per SIMD lane, 160 KB of LDS)
+    const size_t wide = v.storage == LBM_STORE_F64 ? 8 : 4;
+    const int regs = ((wide == 8 ? 44 + 18 * R : 27 + 9 * R) + 7) / 8 * 8;
+    const double m = std::max(1, std::min(std::min(8, 512 / regs) * 4 / t.waves,
+                                          (int)(160 * 1024 / tile_lds(t.waves, wide))));
+    const double per_cu = nb / device_cus();
+    const bool many = per_cu > 4 * m;                     // rounds blur into one another
+    const double n = many ? per_cu + 0.5 * m : std::ceil(per_cu);
+    const double rounds = many ? n / m : std::ceil(n / m);
+    const double issue = n * live * R * c.row / 4;
+    const double latency = rounds * (t.steps * (0.03 * R + 0.1) + c.wg);
+    const double mem = (nb * kTileCols * R * t.waves + (double)v.nx * v.ny) * 9 * storage_bytes(v.storage) / c.bw;
+    return c.t0 + std::max(std::max(issue + c.wg, latency), mem) +
+           (m < 2 && n > 1 ? 0.5 * mem : 0.15 * std::min(issue, mem));
+}
+
+}  // namespace
+
+// Lattices whose nine planes one buffer resource reaches.
+bool tile_fits(const View &v) { return (uint64_t)v.plane * storage_bytes(v.storage) * 9 <= 0xFFFFFFFFull; }
+
+// The tile shape with the least time per step by tile_us; T up to 9 (beyond,
+// the halo outgrows what a launch costs at every size measured).  The shapes
+// offered hold the best one at 16 of 17 sizes of each storage type: more than
+// four rows per lane leave too few waves in flight, fewer than twelve waves
+// too little tile for its halo (FP64 tiles of 64 rows take eight waves of
+// four: with sixteen, one workgroup per compute unit is left).
+TileShape tile_shape(const View &v)
+{
+    static const int32_t shapes[][2] = {{1, 12}, {1, 16}, {2, 12}, {2, 16}, {3, 12}, {3, 16}, {4, 8}, {4, 16}};
+    TileShape best{0, 0, 0};
+    double best_us = INFINITY;
+    if (!tile_fits(v)) return best;
+    for (const auto &s : shapes) {
+        if (s[0] == 4 && (s[1] == 8) != (v.storage == LBM_STORE_F64)) continue;
+        for (int T = 2; T <= 9; ++T) {
+            const TileShape t{s[0], s[1], T};
+            const double us = tile_us(v, t) / T;
+            if (us < best_us) {
+                best_us = us;
+                best = t;
+            }
+        }
+    }
+    return best;
+}
+
+hipError_t launch_tile(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st)
+{
+    if (v.compute == LBM_COMPUTE_F64) return launch_tile_typed<double, double>(v, src, dst, t, steps, st);
+    switch (v.storage) {
+    case LBM_STORE_F64: return launch_tile_typed<double, float>(v, src, dst, t, steps, st);
+    case LBM_STORE_F32: return launch_tile_typed<float, float>(v, src, dst, t, steps, st);
+    case LBM_STORE_F16: return launch_tile_typed<f16_tag, float>(v, src, dst, t, steps, st);
+    case LBM_STORE_BF16: return launch_tile_typed<bf16_tag, float>(v, src, dst, t, steps, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace lbm

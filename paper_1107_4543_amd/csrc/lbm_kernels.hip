@@ -15,6 +15,7 @@
 // v_x != 0 is misaligned by one element.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lbm_step_common.hpp"
@@ -372,31 +373,47 @@ __global__ void k_pool_commit(PoolMember *mem, int nmem, int kk, int T)
 
 // ---- block reductions (fixed order, deterministic) ---------------------------
 
-template <int N>
-__device__ __forceinline__ void block_sum_to(double (&acc)[N], double *out)
+// v plus the value that a DPP control moves into the lane (0 where none does).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
 {
-    __shared__ double red[16][N];
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sum over the wave, in lane 63: shifts within the rows of 16 lanes, then the
+// rows' totals broadcast onward.  18 sums take 324 vector instructions, about
+// 0.7 us; LDS shuffles (__shfl_xor) took 216 LDS instructions and 2 us.
+__device__ __forceinline__ double wave_sum63(double v)
+{
+    v = dpp_add<0x111, 0xf>(v);                         // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);                         // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);                         // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);                         // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);                         // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);                      // row_bcast:31 into rows 2 and 3
+}
+
+// Block sums of N accumulators: red[k] for the whole block after the call.
+template <int N, int BT>
+__device__ __forceinline__ void block_sums(const double (&acc)[N], double (&red)[N])
+{
+    __shared__ double part[BT / 64][N];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        double v = acc[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        acc[k] = v;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) red[wave][k] = acc[k];
+        const double v = wave_sum63(acc[k]);
+        if (lane == 63) part[wave][k] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int k = 0; k < N; ++k) {
-            double s = 0.0;
-            for (int wv = 0; wv < nw; ++wv) s += red[wv][k];
-            out[k] = s;
-        }
+    if ((int)threadIdx.x < N) {
+        double s = 0.0;
+        for (int wv = 0; wv < BT / 64; ++wv) s += part[wv][threadIdx.x];
+        red[threadIdx.x] = s;
     }
+    __syncthreads();
 }
 
 __device__ __forceinline__ void block_max_to(double v, double *out)
@@ -415,29 +432,38 @@ __device__ __forceinline__ void block_max_to(double v, double *out)
     }
 }
 
-// Sums `width` columns of nb partial rows in a fixed order (one block).
-// mode 0: out[k] = sum * mul; mode 1: max.
-__global__ void __launch_bounds__(256) k_final(const double *partials, int nb, int width,
-                                               double mul, int mode, double *out)
+// Sums `width` columns of nb partial rows in a fixed order: one wave per
+// column (one block, 16 waves).  mode 0: sums into out; 1: maxima into out;
+// 2: sums, then the projection's phases (project_finish).  The columns one
+// after another in one block of 256 took 18.5 us for 18 of them.
+struct Mode {
+    int32_t mx, my, nx, ny;
+    double inv_scale;
+};
+
+__device__ __forceinline__ void project_finish(const double *sums, const Mode &m, double *out);
+
+__global__ void __launch_bounds__(1024) k_final(const double *partials, int nb, int width, int mode, Mode pm, double *out)
 {
-    __shared__ double red[256];
-    for (int k = 0; k < width; ++k) {
+    __shared__ double red[32];
+    const int lane = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k < width; k += 16) {
         double s = 0.0;
-        for (int j = threadIdx.x; j < nb; j += blockDim.x) {
+        for (int j = lane; j < nb; j += 64) {
             const double v = partials[(size_t)j * width + k];
             s = mode == 1 ? fmax(s, v) : s + v;
         }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h)
-                red[threadIdx.x] = mode == 1 ? fmax(red[threadIdx.x], red[threadIdx.x + h])
-                                             : red[threadIdx.x] + red[threadIdx.x + h];
-            __syncthreads();
+        if (mode == 1) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s = fmax(s, __shfl_xor(s, off, 64));
+        } else {
+            s = wave_sum63(s);
         }
-        if (threadIdx.x == 0) out[k] = mode == 1 ? red[0] : red[0] * mul;
-        __syncthreads();
+        if (lane == 63) red[k] = s;
     }
+    __syncthreads();
+    if (mode == 2) project_finish(red, pm, out);
+    else if ((int)threadIdx.x < width) out[threadIdx.x] = red[threadIdx.x];
 }
 
 // ---- initialisation, readback, diagnostics ------------------------------------
@@ -553,76 +579,147 @@ __global__ void __launch_bounds__(256) k_write_pop(CellArgs a, const double *f, 
     }
 }
 
-// Global sums of the collision invariants (aligned reads: a global sum does
-// not need the pull shift) and the count of non-finite stored values.
-template <typename S>
-__global__ void __launch_bounds__(256) k_diag(CellArgs a, const typename Store<S>::raw *src, double *partials)
+// Cells of the lattice that a block of a reduction takes: block b has the
+// columns [cols (b mod bx), ...) and every by-th band of h rows, h = threads >>
+// shift, from band b / bx on.  Its threads lie in rows of 2^shift (at least the
+// lattice's width where that is less than the block's), so that a thread
+// keeps its column.  Neighbouring bands go to neighbouring blocks, so that the
+// device sweeps through memory as one front: with a stretch of rows of its own
+// for each block, 4096^2 FP32 diagnostics took 166 us instead of 110.
+struct RedShape {
+    int32_t bx, by, cols, shift;
+    __host__ __device__ int blocks() const { return bx * by; }
+};
+
+RedShape red_shape(const View &v, int threads)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const int64_t n = (int64_t)a.nx * a.ny;
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
-        double r = 0.0, jx = 0.0, jy = 0.0;
-        int bad = 0;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const double g = (double)Store<S>::widen(src[i * a.plane + (int64_t)y * a.pitch + x]);
-            bad += !isfinite(g);
-            r += g;
-            jx += VX_[i] * g;
-            jy += VY_[i] * g;
-        }
-        acc[0] += r;
-        acc[1] += jx;
-        acc[2] += jy;
-        acc[3] += bad;
-    }
-    block_sum_to<4>(acc, partials + (size_t)blockIdx.x * 4);
+    RedShape g;
+    g.shift = 0;
+    while ((1 << g.shift) < threads && (1 << g.shift) < v.nx) ++g.shift;
+    const int w = 1 << g.shift, h = threads >> g.shift;
+    const int tx = (v.nx + w - 1) / w;
+    g.cols = w * ((tx + kRedBlocks - 1) / kRedBlocks);
+    g.bx = (v.nx + g.cols - 1) / g.cols;
+    // at least two cells per thread
+    g.by = std::max(1, std::min(kRedBlocks / g.bx, (v.ny + 2 * h - 1) / (2 * h)));
+    return g;
 }
 
-// sum_y P_i(y) e^{-i k.y}; the pull shift e^{-i k.v_i} is applied afterwards.
-template <typename S>
-__global__ void __launch_bounds__(256) k_project(CellArgs a, const typename Store<S>::raw *src, int mx,
-                                                 int my, double *partials)
+// Threads per block of a reduction: 1024 where 512 blocks of 256 would leave
+// a thread more than eight cells.
+bool red_wide(const View &v) { return (int64_t)v.nx * v.ny > (int64_t)kRedBlocks * 256 * 8; }
+
+// Global sums of the collision invariants (aligned reads: a global sum does
+// not need the pull shift) and the count of non-finite stored values.
+template <typename S, int BT>
+__global__ void __launch_bounds__(BT) k_diag(CellArgs a, RedShape g, const typename Store<S>::raw *src, double *partials)
+{
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    __shared__ double red[4];
+    const int by = (int)blockIdx.x / g.bx, bx = (int)blockIdx.x - by * g.bx;
+    const int x0 = bx * g.cols, x1 = min(a.nx, x0 + g.cols);
+    const int w = 1 << g.shift, h = BT >> g.shift;
+    for (int x = x0 + ((int)threadIdx.x & (w - 1)); x < x1; x += w)
+#pragma unroll 2
+        for (int y = by * h + ((int)threadIdx.x >> g.shift); y < a.ny; y += g.by * h) {
+            const typename Store<S>::raw *p = src + ((int64_t)y * a.pitch + x);
+            double r = 0.0, jx = 0.0, jy = 0.0;
+            int bad = 0;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const double v = (double)Store<S>::widen(p[i * a.plane]);
+                bad += !isfinite(v);
+                r += v;
+                jx += VX_[i] * v;
+                jy += VY_[i] * v;
+            }
+            acc[0] += r;
+            acc[1] += jx;
+            acc[2] += jy;
+            acc[3] += bad;
+        }
+    block_sums<4, BT>(acc, red);
+    if (threadIdx.x < 4) partials[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x];
+}
+
+// e^{-2 pi i m v / n} as (cos, sin) of the exact phase fraction ((m v) mod n) / n,
+// 0 <= m < n, -1 <= v < n.
+__device__ __forceinline__ void phase(int m, int v, int n, double *cs, double *sn)
+{
+    double p;
+    if (n <= 0xffff) {                                  // m v fits 32 bits
+        p = (double)((uint32_t)(m * (v < 0 ? v + n : v)) % (uint32_t)n);
+    } else {
+        int64_t q = ((int64_t)m * v) % n;
+        p = (double)(q < 0 ? q + n : q);
+    }
+    sincospi(2.0 * (p / n), sn, cs);
+}
+
+// out = sums * inv_scale * e^{-i k.v_i} (the pull shift), 9 complex values.
+__device__ __forceinline__ void project_finish(const double *sums, const Mode &m, double *out)
+{
+    const int i = threadIdx.x;
+    if (i >= 9) return;
+    double cx, sx, cy, sy;
+    phase(m.mx, VX_[i], m.nx, &cx, &sx);
+    phase(m.my, VY_[i], m.ny, &cy, &sy);
+    const double cs = cx * cy - sx * sy, sn = sx * cy + cx * sy;
+    const double re = sums[2 * i] * m.inv_scale, im = sums[2 * i + 1] * m.inv_scale;
+    out[2 * i] = re * cs + im * sn;          // (re + i im)(cs - i sn)
+    out[2 * i + 1] = im * cs - re * sn;
+}
+
+// sum_y P_i(y) e^{-i k.y}; the pull shift e^{-i k.v_i} is applied afterwards
+// (project_finish).  The phase separates into a column's and a row's factor:
+// a thread keeps its column's, the rows' are made once per block (256 at a
+// time) and read from LDS, so a cell costs four multiply-adds for its phase
+// instead of two 64-bit divisions and a sincospi.  With the final sums by one
+// wave per column and the phases of the shift in the same launch, a small
+// lattice's projection takes 7.4 us (two launches' latency) instead of 30, and
+// 4096^2 FP32 117 us (5.2 TB/s) instead of 229.
+template <typename S, int BT>
+__global__ void __launch_bounds__(BT) k_project(CellArgs a, RedShape g, const typename Store<S>::raw *src, Mode m,
+                                                double *partials, double *out)
 {
     double acc[18];
 #pragma unroll
     for (int k = 0; k < 18; ++k) acc[k] = 0.0;
-    const int64_t n = (int64_t)a.nx * a.ny;
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
-         c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
-        // exact phase fraction: ((mx x) mod nx)/nx + ((my y) mod ny)/ny
-        int64_t px = ((int64_t)mx * x) % a.nx, py = ((int64_t)my * y) % a.ny;
-        if (px < 0) px += a.nx;
-        if (py < 0) py += a.ny;
-        const double frac = (double)px / a.nx + (double)py / a.ny;
-        double sn, cs;
-        sincospi(2.0 * frac, &sn, &cs);
+    __shared__ double ec[256], es[256], red[18];
+    const int by = (int)blockIdx.x / g.bx, bx = (int)blockIdx.x - by * g.bx;
+    const int x0 = bx * g.cols, x1 = min(a.nx, x0 + g.cols);
+    const int w = 1 << g.shift, hs = __ffs(BT >> g.shift) - 1, h = 1 << hs;
+    // the block's rows by their order in it
+    const int first = by << hs, band = g.by << hs;
+    const int bands = first < a.ny ? (a.ny - first + band - 1) / band : 0;
+    for (int q0 = 0; q0 < bands << hs; q0 += 256) {
+        const int n = min(256, (bands << hs) - q0);
+        const auto row = [&](int q) { return first + ((q0 + q) >> hs) * band + ((q0 + q) & (h - 1)); };
+        if ((int)threadIdx.x < n) phase(m.my, min(row((int)threadIdx.x), a.ny - 1), a.ny, &ec[threadIdx.x], &es[threadIdx.x]);
+        __syncthreads();
+        for (int x = x0 + ((int)threadIdx.x & (w - 1)); x < x1; x += w) {
+            double cx, sx;
+            phase(m.mx, x, a.nx, &cx, &sx);
+#pragma unroll 2
+            for (int q = (int)threadIdx.x >> g.shift; q < n; q += h) {
+                const int y = row(q);
+                if (y >= a.ny) break;
+                const typename Store<S>::raw *p = src + ((int64_t)y * a.pitch + x);
+                const double cy = ec[q], sy = es[q];
+                const double cs = cx * cy - sx * sy, sn = sx * cy + cx * sy;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const double g = (double)Store<S>::widen(src[i * a.plane + (int64_t)y * a.pitch + x]);
-            acc[2 * i] += g * cs;
-            acc[2 * i + 1] -= g * sn;
+                for (int i = 0; i < 9; ++i) {
+                    const double v = (double)Store<S>::widen(p[i * a.plane]);
+                    acc[2 * i] = fmad(v, cs, acc[2 * i]);
+                    acc[2 * i + 1] = fmad(-v, sn, acc[2 * i + 1]);
+                }
+            }
         }
+        __syncthreads();
     }
-    block_sum_to<18>(acc, partials + (size_t)blockIdx.x * 18);
-}
-
-__global__ void k_project_finish(const double *sums, int mx, int my, int nx, int ny, double inv_scale,
-                                 double *out)
-{
-    const int i = threadIdx.x;
-    if (i >= 9) return;
-    int64_t px = ((int64_t)mx * VX_[i]) % nx, py = ((int64_t)my * VY_[i]) % ny;
-    if (px < 0) px += nx;
-    if (py < 0) py += ny;
-    double sn, cs;
-    sincospi(2.0 * ((double)px / nx + (double)py / ny), &sn, &cs);
-    const double re = sums[2 * i] * inv_scale, im = sums[2 * i + 1] * inv_scale;
-    out[2 * i] = re * cs + im * sn;          // (re + i im)(cs - i sn)
-    out[2 * i + 1] = im * cs - re * sn;
+    block_sums<18, BT>(acc, red);
+    if (gridDim.x == 1) project_finish(red, m, out);
+    else if (threadIdx.x < 18) partials[(size_t)blockIdx.x * 18 + threadIdx.x] = red[threadIdx.x];
 }
 
 int grid_for(int64_t n, int block, int cap)
@@ -720,7 +817,7 @@ struct InitF {
         const int g = measure ? kRedBlocks : grid_for(n, 256, 65536);
         hipLaunchKernelGGL(k_init<S>, dim3(g), dim3(256), 0, st, a, rho, ux, uy,
                            (typename Store<S>::raw *)dst, partials, (int)measure);
-        if (measure) hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, st, partials, g, 1, 1.0, 1, result);
+        if (measure) hipLaunchKernelGGL(k_final, dim3(1), dim3(1024), 0, st, partials, g, 1, 1, Mode{}, result);
         return hipGetLastError();
     }
 };
@@ -764,9 +861,12 @@ struct DiagF {
     static hipError_t run(const View &v, const void *src, double *partials, double *result, hipStream_t st)
     {
         const CellArgs a = make_cell_args(v);
-        const int g = grid_for((int64_t)v.nx * v.ny, 256, kRedBlocks);
-        hipLaunchKernelGGL(k_diag<S>, dim3(g), dim3(256), 0, st, a, (const typename Store<S>::raw *)src, partials);
-        hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, st, partials, g, 4, 1.0, 0, result);
+        const bool wide = red_wide(v);
+        const RedShape g = red_shape(v, wide ? 1024 : 256);
+        const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
+        if (wide) hipLaunchKernelGGL((k_diag<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, partials);
+        else hipLaunchKernelGGL((k_diag<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, partials);
+        hipLaunchKernelGGL(k_final, dim3(1), dim3(1024), 0, st, partials, g.blocks(), 4, 0, Mode{}, result);
         return hipGetLastError();
     }
 };
@@ -777,13 +877,16 @@ struct ProjectF {
                           double *out, hipStream_t st)
     {
         const CellArgs a = make_cell_args(v);
-        const int g = grid_for((int64_t)v.nx * v.ny, 256, kRedBlocks);
-        double *sums = partials + (size_t)kRedBlocks * 18;
-        hipLaunchKernelGGL(k_project<S>, dim3(g), dim3(256), 0, st, a, (const typename Store<S>::raw *)src,
-                           (int)mx, (int)my, partials);
-        hipLaunchKernelGGL(k_final, dim3(1), dim3(256), 0, st, partials, g, 18, 1.0, 0, sums);
-        hipLaunchKernelGGL(k_project_finish, dim3(1), dim3(64), 0, st, sums, (int)mx, (int)my, v.nx, v.ny,
-                           v.inv_scale, out);
+        const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
+        const auto mod = [](int32_t k, int32_t n) { return (k % n + n) % n; };
+        const Mode m{mod(mx, v.nx), mod(my, v.ny), v.nx, v.ny, v.inv_scale};
+        const bool wide = red_wide(v);
+        const RedShape g = red_shape(v, wide ? 1024 : 256);
+        if (wide) hipLaunchKernelGGL((k_project<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, m, partials, out);
+        else hipLaunchKernelGGL((k_project<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, m, partials, out);
+        // a lattice of one block has its result already
+        if (g.blocks() > 1)
+            hipLaunchKernelGGL(k_final, dim3(1), dim3(1024), 0, st, partials, g.blocks(), 18, 2, m, out);
         return hipGetLastError();
     }
 };

@@ -365,7 +365,10 @@ typedef struct lbm_pool lbm_pool;
  *                two-wave strip (64 * 2 - 2(T-1) columns, rounded alike)
  *                go to one, run as a second launch beside the first.
  * The tile table holds the one-step tiles and, for T > 1, the strip tasks
- * of every unfinished member. */
+ * of every unfinished member.  While the unfinished members hold few cells
+ * (limits by storage type, 5 * 2^20 to 9 * 2^20) the shared-halo shapes (flags
+ * 32, 34, 96, 98) take register tiles (see lbm_launch) in place of strips, as
+ * far as the tile table has room for them. */
 typedef struct lbm_pool_shape {
     int32_t tile_cells;
     int32_t block;

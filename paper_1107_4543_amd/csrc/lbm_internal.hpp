@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/lbm.h"
 #include "lbm_device.hpp"
 
@@ -51,6 +53,8 @@ struct TileShape {
 };
 bool tile_fits(const View &v);
 TileShape tile_shape(const View &v);
+TileShape tile_shape(const std::vector<const View *> &vs, int T);
+void tile_output(const TileShape &t, int *cols, int *rows);
 hipError_t launch_tile(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st);
 // measure_only: compute max |g| (before scaling) into result[0], store nothing.
 hipError_t launch_init(const View &v, const double *rho, const double *ux, const double *uy,
@@ -153,6 +157,12 @@ hipError_t launch_pool_commit(PoolMember *mem, int nmem, int kk, int T, hipStrea
 void *pool_step_kernel(int cls);
 void *pool_multi_kernel(int cls, int T, int flags);
 void *pool_commit_kernel();
+// The same launch on register tiles of `rows` rows per lane; its further
+// argument is T.  Its dynamic LDS for workgroups of `waves` waves.
+void *pool_tile_kernel(int cls, int rows);
+size_t pool_tile_lds(int cls, int waves);
+hipError_t launch_pool_tile(int range, const TileShape &t, const PoolHeader *hdr, const PoolMember *mem,
+                            const PoolTile *tiles, int j, int grid, hipStream_t st);
 
 }  // namespace lbm
 

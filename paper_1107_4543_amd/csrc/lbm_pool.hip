@@ -23,6 +23,8 @@
 
 #include "lbm_internal.hpp"
 
+using lbm::View;
+
 namespace {
 
 lbm_status pfail(lbm_status s, const char *fmt, ...)
@@ -79,9 +81,10 @@ struct lbm_pool {
     int max_range_tasks = 0;         // largest T-step task range
     int max_range_two = 0;           // largest two-wave task range
     lbm_pool_shape shape{256, 512, 4096, 256, 7, 96, 4, 32};
+    lbm::TileShape tile{};           // register tiles the tables hold in place of strips (steps 0: strips)
     std::vector<Slot> slots;
     std::vector<int> finishing;      // slot indices in completion order
-    std::map<std::tuple<unsigned, unsigned, int, int, int, int, int, int>, GraphEntry> graphs;   // (range masks, steps, steps per T-step launch, one-step launches, grids)
+    std::map<std::tuple<unsigned, unsigned, int, int, int, int, int, int, int, int>, GraphEntry> graphs;   // (range masks, steps, steps per T-step launch, one-step launches, grids, tile shape)
 };
 
 namespace {
@@ -186,6 +189,22 @@ int onestep_tiles_of(const lbm_pool_shape &sh, const lbm_lattice *L)
 
 int tiles_of(const lbm_pool_shape &sh, const lbm_lattice *L) { return onestep_tiles_of(sh, L) + tasks_of(sh, L); }
 
+int64_t tile_tasks(const lbm::TileShape &t, const View &v)
+{
+    int oc, orow;
+    lbm::tile_output(t, &oc, &orow);
+    return (int64_t)((v.nx + oc - 1) / oc) * ((v.ny + orow - 1) / orow);
+}
+
+// Most cells of a pool's unfinished members for register tiles, by storage
+// type.  Measured, us per step, strips -> tiles of the same T: FP32 one 64^2 4.5
+// -> 0.85, 40 of 64-200 (0.55M cells) 7.0 -> 3.4, 20 of 64-1024 (3.2M) 14.3 ->
+// 11.1, 60 of them (8.5M) 33.1 -> 28.8, four 1500^2 (9M) 29.7 -> 29.3, 256 of
+// 64-1024 (30M) 91 -> 120; FP64 60 of 64-1024 62.1 -> 57.8, four 1500^2 53.6 ->
+// 56.1; FP16 40 of 64-200 7.3 -> 4.0, 20 of 64-1024 12.3 -> 11.5, 60 of them 27.3
+// -> 28.8.
+constexpr int64_t kPoolTileCells[4] = {(int64_t)1 << 23, (int64_t)9 << 20, (int64_t)5 << 20, (int64_t)5 << 20};
+
 // Segment height of a pool's table: the shape's seg_rows, or -- when the
 // unfinished members' strips cut at that height give fewer tasks than fill
 // the device once (three four-wave workgroups per compute unit, the count a
@@ -244,6 +263,31 @@ int table_seg_rows(const lbm_pool *P)
     return fits(seg) ? seg : (fits(cap) ? cap : sh.seg_rows);
 }
 
+// Register tiles in place of strips for the unfinished members, or none: with
+// the shared-halo flags, while the members hold few cells (the least of the
+// limits of the storage types present) and the tile table has room for them.
+lbm::TileShape table_tile(const lbm_pool *P)
+{
+    const lbm_pool_shape &sh = P->shape;
+    lbm::TileShape t{};
+    if (!wg_table(sh)) return t;
+    std::vector<const View *> vs;
+    int64_t cells = 0, onestep = 0, most = INT64_MAX;
+    for (const Slot &sl : P->slots) {
+        if (!sl.lat || sl.t_done >= sl.t_target) continue;
+        most = std::min(most, kPoolTileCells[sl.lat->v.storage]);
+        vs.push_back(&sl.lat->v);
+        cells += (int64_t)sl.lat->v.nx * sl.lat->v.ny;
+        onestep += onestep_tiles_of(sh, sl.lat);
+    }
+    if (cells > most) return t;
+    t = lbm::tile_shape(vs, sh.steps_per_launch);
+    if (t.steps == 0) return t;
+    int64_t tasks = 0;
+    for (const View *v : vs) tasks += tile_tasks(t, *v);
+    return onestep + tasks <= P->max_tiles ? t : lbm::TileShape{};
+}
+
 void drop_graphs(lbm_pool *P)
 {
     for (auto &kv : P->graphs) {
@@ -287,6 +331,7 @@ lbm_status upload(lbm_pool *P)
             load[c][best] -= e.first;
         }
     }
+    P->tile = table_tile(P);
     const int seg_rows = table_seg_rows(P);
     struct T { int range; int64_t cells; lbm::PoolTile t; };
     std::vector<T> all, tasks, twos;
@@ -327,7 +372,26 @@ lbm_status upload(lbm_pool *P)
                 t.cells = (int64_t)t.t.nrows * t.t.ncols;
                 all.push_back(t);
             }
-        if (P->shape.steps_per_launch > 1) {
+        if (P->tile.steps) {
+            // tiles of nearly equal height
+            int oc, orow;
+            lbm::tile_output(P->tile, &oc, &orow);
+            const int k = (L->v.ny + orow - 1) / orow;
+            for (int sg = 0; sg < k; ++sg) {
+                const int y0 = (int)((int64_t)L->v.ny * sg / k), y1 = (int)((int64_t)L->v.ny * (sg + 1) / k);
+                for (int x0 = 0; x0 < L->v.nx; x0 += oc) {
+                    T t{};
+                    t.range = m.cls * lbm::kChains + chain[i];
+                    t.t.member = i;
+                    t.t.y0 = y0;
+                    t.t.x0 = x0;
+                    t.t.nrows = y1 - y0;
+                    t.t.ncols = std::min(oc, L->v.nx - x0);
+                    t.cells = t.t.nrows;
+                    tasks.push_back(t);
+                }
+            }
+        } else if (P->shape.steps_per_launch > 1) {
             // four-wave (or one-wave) strips, then a two-wave one
             const bool wg = wg_table(P->shape);
             const WgStrips g = wg ? wg_strips(P->shape, L) : WgStrips{0, 0, 0};
@@ -421,7 +485,7 @@ int launch_grid(const lbm_pool *P)
 // most the shape's grid.
 int multi_grid(const lbm_pool *P)
 {
-    const int per = wg_table(P->shape) ? 1 : P->shape.waves;
+    const int per = wg_table(P->shape) || P->tile.steps ? 1 : P->shape.waves;
     const int need = (P->max_range_tasks + per - 1) / per;
     int g = 1;
     while (g < need && g < P->shape.grid) g *= 2;
@@ -450,7 +514,7 @@ int two_grid(const lbm_pool *P)
 lbm_status get_graph(lbm_pool *P, unsigned mask, unsigned two, int len, int T, int nsingle, hipGraphExec_t *out)
 {
     const int grid = launch_grid(P), mgrid = multi_grid(P), tgrid = two_grid(P);
-    auto key = std::make_tuple(mask, two, len, T, nsingle, grid, mgrid, tgrid);
+    auto key = std::make_tuple(mask, two, len, T, nsingle, grid, mgrid, tgrid, P->tile.rows, P->tile.waves);
     auto it = P->graphs.find(key);
     if (it != P->graphs.end()) {
         *out = it->second.exec;
@@ -474,16 +538,19 @@ lbm_status get_graph(lbm_pool *P, unsigned mask, unsigned two, int len, int T, i
             // workgroups; kind 1: T-step of two-wave workgroups
             for (int kind = 0; kind < (multi && (two & (1u << r)) ? 2 : 1); ++kind) {
                 int range = r, idx = multi ? k : k - nmulti, kk = len, TT = T;
-                void *margs[] = {(void *)&hdr, (void *)&mem, (void *)&tiles, (void *)&range, (void *)&idx};
+                // a strip kernel takes the first five, a tile kernel six
+                void *margs[] = {(void *)&hdr, (void *)&mem, (void *)&tiles, (void *)&range, (void *)&idx, (void *)&TT};
                 void *sargs[] = {(void *)&hdr, (void *)&mem, (void *)&tiles, (void *)&range, (void *)&idx, (void *)&kk,
                                  (void *)&TT};
                 hipKernelNodeParams np{};
-                np.func = !multi    ? lbm::pool_step_kernel(c)
+                const bool tile = multi && P->tile.steps;
+                np.func = tile      ? lbm::pool_tile_kernel(c, P->tile.rows)
+                          : !multi  ? lbm::pool_step_kernel(c)
                           : kind    ? lbm::pool_multi_kernel(c, T, kernel_flags(P->shape) | lbm::kWgTwo)
                                     : lbm::pool_multi_kernel(c, T, kernel_flags(P->shape));
                 np.gridDim = dim3(!multi ? grid : kind ? tgrid : mgrid);
-                np.blockDim = !multi ? dim3(P->shape.block) : dim3(64, kind ? 2 : P->shape.waves);
-                np.sharedMemBytes = 0;
+                np.blockDim = !multi ? dim3(P->shape.block) : dim3(64, tile ? P->tile.waves : kind ? 2 : P->shape.waves);
+                np.sharedMemBytes = tile ? (unsigned)lbm::pool_tile_lds(c, P->tile.waves) : 0;
                 np.kernelParams = multi ? margs : sargs;
                 np.extra = nullptr;
                 hipGraphNode_t n;
@@ -531,6 +598,7 @@ int chunk_steps(const lbm_pool *P, int kk)
 {
     const int T = P->shape.steps_per_launch;
     if (T < 2 || kk >= T || kk < 2) return T;
+    if (P->tile.steps) return kk;                        // tiles take any step count up to T
     for (int r = 0; r < lbm::kRanges; ++r) {
         if (!(P->range_mask & (1u << r))) continue;
         if (!lbm::pool_multi_kernel(r / lbm::kChains, kk, kernel_flags(P->shape))) return T;
@@ -857,7 +925,10 @@ lbm_status lbm_pool_time_launches(lbm_pool *pool, int32_t reps, double *avg_us)
     auto launch_all = [&]() -> hipError_t {
         for (int c = 0; c < lbm::kRanges; ++c) {
             if (!(pool->range_mask & (1u << c))) continue;
-            hipError_t r = T > 1 ? lbm::launch_pool_multi(c, T, kernel_flags(pool->shape), pool->d_hdr, pool->d_mem,
+            hipError_t r = pool->tile.steps
+                               ? lbm::launch_pool_tile(c, pool->tile, pool->d_hdr, pool->d_mem, pool->d_tiles, 0,
+                                                       multi_grid(pool), pool->stream)
+                           : T > 1 ? lbm::launch_pool_multi(c, T, kernel_flags(pool->shape), pool->d_hdr, pool->d_mem,
                                                           pool->d_tiles, 0, multi_grid(pool), pool->shape.waves,
                                                           pool->stream)
                                  : lbm::launch_pool_step(c, pool->d_hdr, pool->d_mem, pool->d_tiles, 0, 1, 1,

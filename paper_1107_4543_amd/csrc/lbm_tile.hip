@@ -23,6 +23,7 @@
 // 600 x 430 3.9 -> 1.7.
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "lbm_step_common.hpp"
 
@@ -91,38 +92,35 @@ __device__ __forceinline__ V left(V v) { return shift0<kDppWaveShr1>(v); }
 template <typename V>
 __device__ __forceinline__ V right(V v) { return shift0<kDppWaveShl1>(v); }
 
+// T steps of the tile whose `rows` x `cols` output cells start at (x0, y0), by
+// the calling workgroup (every wave with the same arguments).
 template <typename S, typename C, int R>
-__global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(TileArgs<C> a)
+__device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, int ny, int pitch, int64_t plane,
+                                          const Relax<C> &relax, float scale, float inv_scale, int T, int x0, int y0,
+                                          int rows, int cols, char *lds)
 {
     using Raw = typename Store<S>::raw;
     using W = typename Store<S>::wide;
     constexpr uint32_t E = sizeof(Raw);
-    extern __shared__ char lds[];
     const int lane = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.y), nw = (int)blockDim.y;
-    const int T = a.T;
-    const int bid = remap_xcd((int)blockIdx.x, a.nblocks);
-    const int ty = a.inv_tiles_x ? (int)__umulhi((uint32_t)bid, a.inv_tiles_x) : bid / a.tiles_x;
-    const int tx = bid - ty * a.tiles_x;
-    const int x0 = tx * a.out_cols, y0 = ty * a.out_rows;
-    const int rows = min(a.out_rows, a.ny - y0);          // rows to write
     const int need = rows + 2 * (T - 1);                  // tile rows they depend on
     const int lo = wv * R;                                // first tile row of the wave
     const int xl = x0 + lane - (T - 1);
-    const int c = wrap_near(xl, a.nx);
+    const int c = wrap_near(xl, nx);
     const uint32_t c0 = (uint32_t)c * E;
-    const uint32_t cm = (uint32_t)((c == 0 ? a.nx : c) - 1) * E;
-    const uint32_t cp = (uint32_t)((c + 1 == a.nx) ? 0 : c + 1) * E;
-    const uint32_t pb = (uint32_t)a.plane * E, rb = (uint32_t)a.pitch * E;
-    const __amdgpu_buffer_rsrc_t src = whole_rsrc((const char *)a.src), dst = whole_rsrc((const char *)a.dst);
+    const uint32_t cm = (uint32_t)((c == 0 ? nx : c) - 1) * E;
+    const uint32_t cp = (uint32_t)((c + 1 == nx) ? 0 : c + 1) * E;
+    const uint32_t pb = (uint32_t)plane * E, rb = (uint32_t)pitch * E;
+    const __amdgpu_buffer_rsrc_t src = whole_rsrc((const char *)src_), dst = whole_rsrc((const char *)dst_);
     W w[R][9];
     if (lo < need) {
         int y = y0 - (T - 1) + lo;
-        y = a.ny < 64 ? __builtin_amdgcn_readfirstlane(wrap_mod(y, a.ny)) : y < 0 ? y + a.ny : y >= a.ny ? y - a.ny : y;
-        int ym = (y == 0 ? a.ny : y) - 1;
+        y = ny < 64 ? __builtin_amdgcn_readfirstlane(wrap_mod(y, ny)) : y < 0 ? y + ny : y >= ny ? y - ny : y;
+        int ym = (y == 0 ? ny : y) - 1;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int yp = (y + 1 == a.ny) ? 0 : y + 1;
+            const int yp = (y + 1 == ny) ? 0 : y + 1;
             const uint32_t r0 = (uint32_t)y * rb, rm = (uint32_t)ym * rb, rp = (uint32_t)yp * rb;
             w[j][0] = ld_buf<S, false>(src, c0, r0);
             w[j][1] = ld_buf<S, false>(src, cm, 1 * pb + r0);
@@ -144,7 +142,7 @@ __global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(Til
     const W *const below = (W *)lds + (wv > 0 ? wv - 1 : 0) * (2 * 6 * kTileXch) + lane + 1;
     const W *const above = (W *)lds + (wv + 1 < nw ? wv + 1 : wv) * (2 * 6 * kTileXch) + lane + 1;
     auto update = [&](int j) {
-        cell_update<S, C>(w[j], a.r, a.scale, a.inv_scale);
+        cell_update<S, C>(w[j], relax, scale, inv_scale);
         round_trip9<S>(w[j]);
     };
     auto step = [&](int k, auto par) {
@@ -199,17 +197,61 @@ __global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(Til
     }
     if (k + 1 < T) step(k, std::integral_constant<int, 0>{});
     if (lo + R <= T - 1 || lo >= T - 1 + rows) return;
-    const bool col = lane >= T - 1 && lane < T - 1 + a.out_cols && xl < a.nx;
+    const bool col = lane >= T - 1 && lane < T - 1 + cols && xl < nx;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const int tr = lo + j - (T - 1);                  // row of the tile's output
         if (tr < 0 || tr >= rows) continue;               // wave-uniform
-        cell_update<S, C>(w[j], a.r, a.scale, a.inv_scale);
+        cell_update<S, C>(w[j], relax, scale, inv_scale);
         const uint32_t ro = (uint32_t)(y0 + tr) * rb;
         if (col) {
 #pragma unroll
             for (int i = 0; i < 9; ++i) st_buf<S>(dst, c0, (uint32_t)i * pb + ro, w[j][i]);
         }
+    }
+}
+
+template <typename S, typename C, int R>
+__global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(TileArgs<C> a)
+{
+    extern __shared__ char lds[];
+    const int bid = remap_xcd((int)blockIdx.x, a.nblocks);
+    const int ty = a.inv_tiles_x ? (int)__umulhi((uint32_t)bid, a.inv_tiles_x) : bid / a.tiles_x;
+    const int x0 = (bid - ty * a.tiles_x) * a.out_cols, y0 = ty * a.out_rows;
+    tile_pass<S, C, R>(a.src, a.dst, a.nx, a.ny, a.pitch, a.plane, a.r, a.scale, a.inv_scale, a.T, x0, y0,
+                       min(a.out_rows, a.ny - y0), a.out_cols, lds);
+}
+
+// k_pool_multi's launch j on tile tasks: each workgroup takes tiles in turn.
+template <typename S, typename C, int R>
+__global__ void __launch_bounds__((64 * tile_max_waves<S, R>()))
+k_pool_tile(const PoolHeader *__restrict__ hdr, const PoolMember *__restrict__ mem, const PoolTile *__restrict__ tiles,
+            int range, int j, int T)
+{
+    extern __shared__ char lds[];
+    const int begin = hdr->mbegin[range], end = hdr->mend[range];
+    for (int v = (int)blockIdx.x; v < end - begin; v += (int)gridDim.x) {
+        const PoolTile tile = tiles[begin + xcd_group(v, end - begin)];   // workgroup-uniform
+        const PoolMember *m = mem + tile.member;
+        if ((int64_t)(j + 1) * T > m->t_target - m->t_done) continue;
+        const int par = (int)((m->cur0 + m->flips + j) & 1);
+        tile_pass<S, C, R>(m->buf[par], (void *)m->buf[par ^ 1], m->nx, m->ny, m->pitch, m->plane, member_relax<C>(m),
+                           m->scale, m->inv_scale, T, tile.x0, tile.y0, tile.nrows, tile.ncols, lds);
+        // every wave's reads of this tile's last exchange end before any
+        // wave writes the next tile's
+        __syncthreads();
+    }
+}
+
+template <typename S, typename C>
+void *pool_tile_fn(int rows)
+{
+    switch (rows) {
+    case 1: return reinterpret_cast<void *>(&k_pool_tile<S, C, 1>);
+    case 2: return reinterpret_cast<void *>(&k_pool_tile<S, C, 2>);
+    case 3: return reinterpret_cast<void *>(&k_pool_tile<S, C, 3>);
+    case 4: return reinterpret_cast<void *>(&k_pool_tile<S, C, 4>);
+    default: return nullptr;
     }
 }
 
@@ -227,8 +269,7 @@ hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const Ti
     a.scale = (float)v.scale;
     a.inv_scale = (float)v.inv_scale;
     a.T = steps;
-    a.out_cols = kTileCols - 2 * (steps - 1);
-    a.out_rows = t.rows * t.waves - 2 * (steps - 1);
+    tile_output({t.rows, t.waves, steps}, &a.out_cols, &a.out_rows);
     if (steps < 1 || a.out_cols < 1 || a.out_rows < 1 || !tile_fits(v)) return hipErrorInvalidValue;
     a.tiles_x = (v.nx + a.out_cols - 1) / a.out_cols;
     a.nblocks = a.tiles_x * ((v.ny + a.out_rows - 1) / a.out_rows);
@@ -263,30 +304,57 @@ constexpr TileCost kTileCost[4] = {{1.99, 0.205, 1.70, 6.1e6},    // FP64
                                    {1.43, 0.139, 2.11, 3.75e6},   // FP16
                                    {2.02, 0.134, 1.50, 3.75e6}};  // BF16
 
-double tile_us(const View &v, const TileShape &t)
+// What a launch of shape t on a lattice consists of: tiles, the wave-steps of
+// all of them, cells moved to and from memory.
+struct TileLoad {
+    double tiles = 0, live = 0, cells = 0;
+    bool add(const View &v, const TileShape &t)
+    {
+        const int h = t.steps - 1, R = t.rows;
+        const int oc = kTileCols - 2 * h, orow = R * t.waves - 2 * h;
+        if (oc < 8 || orow < 1) return false;
+        const double n = (double)((v.nx + oc - 1) / oc) * ((v.ny + orow - 1) / orow);
+        const int need = std::min(orow, v.ny) + 2 * h;
+        int w_live = 0;
+        for (int w = 0; w * R < need; ++w) w_live += std::min(t.steps, std::min(w * R + R, need - w * R));
+        tiles += n;
+        live += n * w_live;
+        cells += n * kTileCols * R * t.waves + (double)v.nx * v.ny;
+        return true;
+    }
+};
+
+double tile_us(int storage, const TileShape &t, const TileLoad &l)
 {
-    const TileCost &c = kTileCost[v.storage];
-    const int h = t.steps - 1, R = t.rows;
-    const int oc = kTileCols - 2 * h, orow = R * t.waves - 2 * h;
-    if (oc < 8 || orow < 1) return INFINITY;
-    const double nb = (double)((v.nx + oc - 1) / oc) * ((v.ny + orow - 1) / orow);
-    const int need = std::min(orow, v.ny) + 2 * h;
-    int live = 0;                                         // wave-steps of a tile
-    for (int w = 0; w * R < need; ++w) live += std::min(t.steps, std::min(w * R + R, need - w * R));
+    const TileCost &c = kTileCost[storage];
+    const int R = t.rows;
     // workgroups resident per compute unit (512 registers per SIMD lane, 160 KB of LDS)
-    const size_t wide = v.storage == LBM_STORE_F64 ? 8 : 4;
+    const size_t wide = storage == LBM_STORE_F64 ? 8 : 4;
     const int regs = ((wide == 8 ? 44 + 18 * R : 27 + 9 * R) + 7) / 8 * 8;
     const double m = std::max(1, std::min(std::min(8, 512 / regs) * 4 / t.waves,
                                           (int)(160 * 1024 / tile_lds(t.waves, wide))));
-    const double per_cu = nb / device_cus();
+    const double per_cu = l.tiles / device_cus();
     const bool many = per_cu > 4 * m;                     // rounds blur into one another
     const double n = many ? per_cu + 0.5 * m : std::ceil(per_cu);
     const double rounds = many ? n / m : std::ceil(n / m);
-    const double issue = n * live * R * c.row / 4;
+    const double issue = n * (l.live / l.tiles) * R * c.row / 4;
     const double latency = rounds * (t.steps * (0.03 * R + 0.1) + c.wg);
-    const double mem = (nb * kTileCols * R * t.waves + (double)v.nx * v.ny) * 9 * storage_bytes(v.storage) / c.bw;
+    const double mem = l.cells * 9 * storage_bytes(storage) / c.bw;
     return c.t0 + std::max(std::max(issue + c.wg, latency), mem) +
            (m < 2 && n > 1 ? 0.5 * mem : 0.15 * std::min(issue, mem));
+}
+
+// The tile shapes in use hold the best one at 16 of 17 sizes of each storage
+// type: more than four rows per lane leave too few waves in flight, fewer than
+// twelve waves too little tile for its halo.  Four rows: FP64 with eight waves
+// (with sixteen, one workgroup per compute unit is left), 16-bit with sixteen
+// (not in a pool, whose kernel then takes more than 64 registers, which halves
+// the waves in flight: 60 FP16 members of 8.5M cells 41 us per step).
+constexpr int32_t kTileShapes[][2] = {{1, 12}, {1, 16}, {2, 12}, {2, 16}, {3, 12}, {3, 16}, {4, 8}, {4, 16}};
+bool tile_shape_used(int storage, const int32_t s[2], bool pool)
+{
+    if (s[0] < 4) return true;
+    return s[1] == 8 ? storage == LBM_STORE_F64 : storage >= LBM_STORE_F16 && !pool;
 }
 
 }  // namespace
@@ -295,22 +363,19 @@ double tile_us(const View &v, const TileShape &t)
 bool tile_fits(const View &v) { return (uint64_t)v.plane * storage_bytes(v.storage) * 9 <= 0xFFFFFFFFull; }
 
 // The tile shape with the least time per step by tile_us; T up to 9 (beyond,
-// the halo outgrows what a launch costs at every size measured).  The shapes
-// offered hold the best one at 16 of 17 sizes of each storage type: more than
-// four rows per lane leave too few waves in flight, fewer than twelve waves
-// too little tile for its halo (FP64 tiles of 64 rows take eight waves of
-// four: with sixteen, one workgroup per compute unit is left).
+// the halo outgrows what a launch costs at every size measured).
 TileShape tile_shape(const View &v)
 {
-    static const int32_t shapes[][2] = {{1, 12}, {1, 16}, {2, 12}, {2, 16}, {3, 12}, {3, 16}, {4, 8}, {4, 16}};
     TileShape best{0, 0, 0};
     double best_us = INFINITY;
     if (!tile_fits(v)) return best;
-    for (const auto &s : shapes) {
-        if (s[0] == 4 && (s[1] == 8) != (v.storage == LBM_STORE_F64)) continue;
+    for (const auto &s : kTileShapes) {
+        if (!tile_shape_used(v.storage, s, false)) continue;
         for (int T = 2; T <= 9; ++T) {
             const TileShape t{s[0], s[1], T};
-            const double us = tile_us(v, t) / T;
+            TileLoad l;
+            if (!l.add(v, t)) continue;
+            const double us = tile_us(v.storage, t, l) / T;
             if (us < best_us) {
                 best_us = us;
                 best = t;
@@ -319,6 +384,63 @@ TileShape tile_shape(const View &v)
     }
     return best;
 }
+
+// The same for T-step launches of several lattices together, at the T given.
+TileShape tile_shape(const std::vector<const View *> &vs, int T)
+{
+    TileShape best{0, 0, 0};
+    double best_us = INFINITY;
+    int storage = LBM_STORE_BF16;                         // the widest present
+    for (const View *v : vs) {
+        if (!tile_fits(*v)) return best;
+        storage = std::min(storage, v->storage);
+    }
+    for (const auto &s : kTileShapes) {
+        if (!tile_shape_used(storage, s, true)) continue;
+        const TileShape t{s[0], s[1], T};
+        TileLoad l;
+        bool ok = !vs.empty();
+        for (const View *v : vs) ok = ok && l.add(*v, t);
+        const double us = ok ? tile_us(storage, t, l) : INFINITY;
+        if (us < best_us) {
+            best_us = us;
+            best = t;
+        }
+    }
+    return best;
+}
+
+// Output columns and rows of a tile.
+void tile_output(const TileShape &t, int *cols, int *rows)
+{
+    *cols = kTileCols - 2 * (t.steps - 1);
+    *rows = t.rows * t.waves - 2 * (t.steps - 1);
+}
+
+void *pool_tile_kernel(int cls, int rows)
+{
+    switch (cls) {
+    case LBM_STORE_F64 * 2 + LBM_COMPUTE_F64: return pool_tile_fn<double, double>(rows);
+    case LBM_STORE_F64 * 2 + LBM_COMPUTE_F32: return pool_tile_fn<double, float>(rows);
+    case LBM_STORE_F32 * 2 + LBM_COMPUTE_F32: return pool_tile_fn<float, float>(rows);
+    case LBM_STORE_F16 * 2 + LBM_COMPUTE_F32: return pool_tile_fn<f16_tag, float>(rows);
+    case LBM_STORE_BF16 * 2 + LBM_COMPUTE_F32: return pool_tile_fn<bf16_tag, float>(rows);
+    default: return nullptr;
+    }
+}
+
+hipError_t launch_pool_tile(int range, const TileShape &t, const PoolHeader *hdr, const PoolMember *mem,
+                            const PoolTile *tiles, int j, int grid, hipStream_t st)
+{
+    const int cls = range / kChains;
+    void *f = pool_tile_kernel(cls, t.rows);
+    if (!f) return hipErrorInvalidValue;
+    int T = t.steps;
+    void *args[] = {(void *)&hdr, (void *)&mem, (void *)&tiles, (void *)&range, (void *)&j, (void *)&T};
+    return hipLaunchKernel(f, dim3(grid), dim3(64, t.waves), args, pool_tile_lds(cls, t.waves), st);
+}
+
+size_t pool_tile_lds(int cls, int waves) { return tile_lds(waves, cls / 2 == LBM_STORE_F64 ? 8 : 4); }
 
 hipError_t launch_tile(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st)
 {

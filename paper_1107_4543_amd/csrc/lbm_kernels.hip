@@ -469,7 +469,9 @@ __global__ void __launch_bounds__(1024) k_final(const double *partials, int nb, 
 // ---- initialisation, readback, diagnostics ------------------------------------
 
 struct CellArgs {
-    int32_t nx, ny, pitch, pad;
+    int32_t nx, ny, pitch;
+    int32_t div_shift;        // cell / nx = cell * div_mul >> div_shift
+    uint32_t div_mul;
     int64_t plane;
     double scale, inv_scale;
     Relax<double> r;
@@ -482,7 +484,12 @@ CellArgs make_cell_args(const View &v)
     c.nx = v.nx;
     c.ny = v.ny;
     c.pitch = v.pitch;
-    c.pad = 0;
+    // exact for cell numbers below 2^31, which nx * ny <= pitch * ny keeps to:
+    // mul = ceil(2^(31 + l) / nx) < 2^32 with 2^l >= nx
+    int l = 0;
+    while (((int64_t)1 << l) < v.nx) ++l;
+    c.div_shift = 31 + l;
+    c.div_mul = (uint32_t)((((uint64_t)1 << c.div_shift) + v.nx - 1) / v.nx);
     c.plane = v.plane;
     c.scale = v.scale;
     c.inv_scale = v.inv_scale;
@@ -491,11 +498,59 @@ CellArgs make_cell_args(const View &v)
     return c;
 }
 
+// Row and column of cell c of the row-major fields.
+__device__ __forceinline__ void cell_xy(const CellArgs &a, int64_t c, int &x, int &y)
+{
+    y = (int)((uint64_t)(uint32_t)c * a.div_mul >> a.div_shift);
+    x = (int)c - y * a.nx;
+}
+
 __device__ __forceinline__ int wrap(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+// x / B, correctly rounded, for B = 6 or 9: the rounded reciprocal is half a
+// unit roundoff off, so x times it is within one unit in the last place of
+// the quotient, and one residual step rounds correctly (Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000", 1990, theorem on
+// division by fused multiply-add).  Infinities and NaN pass through.
+template <int B>
+__device__ __forceinline__ double div_by(double x)
+{
+    constexpr double r = 1.0 / B;
+    const double q = x * r;
+    const double c = fmad(fmad(-(double)B, q, x), r, q);
+    return isfinite(q) ? c : q;
+}
+
+// back_transform of an equilibrium deviation, whose dm[5] = -dm[1] and dm[6] =
+// -dm[2], with five divisions in place of eleven (the quotients by 18 and 36 are
+// the one by 9 halved, which is exact, those by 12 the one by 6), each of them
+// by its constant: the same values.  General divisions took as long as the
+// memory traffic of the whole kernel (4096^2 FP32: 280 us with a 64-bit division
+// for the cell's row, now 216; the pass that only measures 232, now 126).
+__device__ __forceinline__ void back_transform_eq(const double dm[9], double f[9])
+{
+    const double r = div_by<9>(dm[0]);
+    const double ex = div_by<6>(dm[1]), ey = div_by<6>(dm[2]);
+    const double e9 = div_by<9>(dm[3]), s9 = div_by<9>(dm[4]);
+    const double ea = -(0.25 * e9) - 0.5 * s9;
+    const double ed = 0.5 * e9 + 0.25 * s9;
+    const double qx = -ex, qy = -ey;
+    const double qxd = 0.5 * qx, qyd = 0.5 * qy;
+    const double pxx = 0.25 * dm[7], pxy = 0.25 * dm[8];
+    f[0] = r - e9 + s9;
+    f[1] = r + ex + ea - qx + pxx;
+    f[2] = r + ey + ea - qy - pxx;
+    f[3] = r - ex + ea + qx + pxx;
+    f[4] = r - ey + ea + qy - pxx;
+    f[5] = r + ex + ey + ed + qxd + qyd + pxy;
+    f[6] = r - ex + ey + ed - qxd + qyd - pxy;
+    f[7] = r - ex - ey + ed - qxd - qyd + pxy;
+    f[8] = r + ex - ey + ed + qxd - qyd - pxy;
+}
 
 // g(x) = M^{-1} dmeq(rho - rho0, rho u - j0), FP64; stored at P_i(x - v_i).
 template <typename S>
-__global__ void __launch_bounds__(256) k_init(CellArgs a, const double *rho, const double *ux,
+__global__ void __launch_bounds__(1024) k_init(CellArgs a, const double *rho, const double *ux,
                                               const double *uy, typename Store<S>::raw *dst,
                                               double *partials, int measure_only)
 {
@@ -504,11 +559,12 @@ __global__ void __launch_bounds__(256) k_init(CellArgs a, const double *rho, con
     double mx = 0.0;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
          c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
+        int x, y;
+        cell_xy(a, c, x, y);
         const double r = rho[c];
         double dm[9], g[9];
         delta_meq<double>(r - a.r.rho0, r * ux[c] - a.r.j0x, r * uy[c] - a.r.j0y, a.r, dm);
-        back_transform<double>(dm, g);
+        back_transform_eq(dm, g);
 #pragma unroll
         for (int i = 0; i < 9; ++i) mx = fmax(mx, fabs(g[i]));
         if (!measure_only) {
@@ -530,7 +586,8 @@ __global__ void __launch_bounds__(256) k_moments(CellArgs a, const typename Stor
     const int64_t n = (int64_t)a.nx * a.ny;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
          c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
+        int x, y;
+        cell_xy(a, c, x, y);
         double r = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
@@ -553,7 +610,8 @@ __global__ void __launch_bounds__(256) k_read_pop(CellArgs a, const typename Sto
     const int64_t n = (int64_t)a.nx * a.ny;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
          c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
+        int x, y;
+        cell_xy(a, c, x, y);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int xs = wrap(x - VX_[i], a.nx), ys = wrap(y - VY_[i], a.ny);
@@ -570,7 +628,8 @@ __global__ void __launch_bounds__(256) k_write_pop(CellArgs a, const double *f, 
     const int64_t n = (int64_t)a.nx * a.ny;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n;
          c += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(c / a.nx), x = (int)(c - (int64_t)y * a.nx);
+        int x, y;
+        cell_xy(a, c, x, y);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int xs = wrap(x - VX_[i], a.nx), ys = wrap(y - VY_[i], a.ny);
@@ -815,7 +874,7 @@ struct InitF {
         const CellArgs a = make_cell_args(v);
         const int64_t n = (int64_t)v.nx * v.ny;
         const int g = measure ? kRedBlocks : grid_for(n, 256, 65536);
-        hipLaunchKernelGGL(k_init<S>, dim3(g), dim3(256), 0, st, a, rho, ux, uy,
+        hipLaunchKernelGGL(k_init<S>, dim3(g), dim3(measure && n > kRedBlocks * 256 ? 1024 : 256), 0, st, a, rho, ux, uy,
                            (typename Store<S>::raw *)dst, partials, (int)measure);
         if (measure) hipLaunchKernelGGL(k_final, dim3(1), dim3(1024), 0, st, partials, g, 1, 1, Mode{}, result);
         return hipGetLastError();

@@ -48,6 +48,7 @@ struct Slot {
     int64_t flips = 0;               // launches taken (buffer swaps) since added
     int cur0 = 0;
     bool finishing = false;          // reached t_target; waiting for poll
+    int tiles = 0;                   // table entries while unfinished (tiles_of at the pool's shape)
     hipEvent_t ev_in = nullptr;      // lattice stream -> pool stream
     hipEvent_t ev_done = nullptr;    // pool stream -> lattice stream
 };
@@ -74,6 +75,11 @@ struct lbm_pool {
     hipEvent_t ev_stage = nullptr;
     bool stage_pending = false;
     bool dirty = true;
+    // One-step tiles are most of a table's entries and are needed only by
+    // chunks with one-step launches: they join the tables with the first such
+    // chunk (256 lattices of 3e7 cells whose steps all end together: 2.7 ms of
+    // host time per lbm_pool_step with them, 0.8 without).
+    bool want_onestep = false, has_onestep = false;
     unsigned range_mask = 0;         // table ranges (class * kChains + chain) with tiles
     int ntiles = 0;
     unsigned two_mask = 0;           // table ranges with two-wave strip tasks
@@ -300,7 +306,8 @@ void drop_graphs(lbm_pool *P)
 // Rebuilds the member and tile tables on the host and uploads them.
 lbm_status upload(lbm_pool *P)
 {
-    if (!P->dirty) return LBM_OK;
+    const bool onestep = P->want_onestep || P->shape.steps_per_launch < 2;
+    if (!P->dirty && (P->has_onestep || !onestep)) return LBM_OK;
     hipError_t e;
     if (P->stage_pending) {
         if ((e = hipEventSynchronize(P->ev_stage)) != hipSuccess) return phip(e, "hipEventSynchronize");
@@ -335,6 +342,8 @@ lbm_status upload(lbm_pool *P)
     const int seg_rows = table_seg_rows(P);
     struct T { int range; int64_t cells; lbm::PoolTile t; };
     std::vector<T> all, tasks, twos;
+    static_assert(lbm::kRanges <= 32, "range mask bits");
+    unsigned mask = 0;
     for (int i = 0; i < P->max_members; ++i) {
         const Slot &s = P->slots[i];
         lbm::PoolMember &m = mem[i];
@@ -359,8 +368,9 @@ lbm_status upload(lbm_pool *P)
         m.inv_scale = (float)L->v.inv_scale;
         m.cls = class_of(L);
         if (s.t_done >= s.t_target) continue;        // finished: no tiles
+        mask |= 1u << (m.cls * lbm::kChains + chain[i]);
         const int r = tile_rows(P->shape, L), cw = tile_cols(P->shape, L);
-        for (int y0 = 0; y0 < L->v.ny; y0 += r)
+        for (int y0 = 0; onestep && y0 < L->v.ny; y0 += r)
             for (int x0 = 0; x0 < L->v.nx; x0 += cw) {
                 T t{};
                 t.range = m.cls * lbm::kChains + chain[i];
@@ -424,16 +434,15 @@ lbm_status upload(lbm_pool *P)
     std::stable_sort(twos.begin(), twos.end(), order);
     const size_t ntot = all.size() + tasks.size() + twos.size();
     if ((int64_t)ntot > P->max_tiles) return pfail(LBM_E_NOMEM, "pool needs %zu tiles, has %d", ntot, P->max_tiles);
-    static_assert(lbm::kRanges <= 32, "range mask bits");
-    unsigned mask = 0;
     for (int c = 0; c < lbm::kRanges; ++c)
         hdr->begin[c] = hdr->end[c] = hdr->mbegin[c] = hdr->mend[c] = hdr->hbegin[c] = hdr->hend[c] = 0;
+    unsigned omask = 0;
     for (size_t j = 0; j < all.size(); ++j) {
         tiles[j] = all[j].t;
         const int c = all[j].range;
-        if (!(mask & (1u << c))) hdr->begin[c] = (int)j;
+        if (!(omask & (1u << c))) hdr->begin[c] = (int)j;
         hdr->end[c] = (int)j + 1;
-        mask |= 1u << c;
+        omask |= 1u << c;
     }
     unsigned tmask = 0;
     for (size_t j = 0; j < tasks.size(); ++j) {
@@ -467,6 +476,7 @@ lbm_status upload(lbm_pool *P)
     P->stage_pending = true;
     P->range_mask = mask;
     P->two_mask = hmask;
+    P->has_onestep = onestep;
     P->dirty = false;
     return LBM_OK;
 }
@@ -624,7 +634,12 @@ lbm_status run_chunk(lbm_pool *P, int kk)
         need = std::max(need, std::min<int64_t>(rem, kk) - lbm::member_multi(rem, kk, T) * T);
     }
     need = std::min<int64_t>(need, lbm::chunk_single_launches(kk, T));
-    lbm_status st = get_graph(P, P->range_mask, P->two_mask, kk, T, (int)need, &ex);
+    lbm_status st;
+    if (need > 0 && !P->has_onestep) {
+        P->want_onestep = true;
+        if ((st = upload(P)) != LBM_OK) return st;
+    }
+    st = get_graph(P, P->range_mask, P->two_mask, kk, T, (int)need, &ex);
     if (st != LBM_OK) return st;
     if ((e = hipGraphLaunch(ex, P->stream)) != hipSuccess) return phip(e, "hipGraphLaunch");
     for (int i = 0; i < P->max_members; ++i) {
@@ -761,11 +776,12 @@ lbm_status lbm_pool_add(lbm_pool *pool, lbm_lattice *lat, int64_t nsteps)
         if (!s.lat) {
             if (free_slot < 0) free_slot = i;
         } else if (s.t_done < s.t_target) {
-            tiles += tiles_of(pool->shape, s.lat);
+            tiles += s.tiles;
         }
     }
     if (free_slot < 0) return pfail(LBM_E_NOMEM, "pool is full (%d members)", pool->max_members);
-    if (tiles + tiles_of(pool->shape, lat) > pool->max_tiles)
+    const int own = tiles_of(pool->shape, lat);
+    if (tiles + own > pool->max_tiles)
         return pfail(LBM_E_NOMEM, "pool tile table is full (%d tiles)", pool->max_tiles);
     Slot &s = pool->slots[free_slot];
     hipError_t e;
@@ -778,6 +794,7 @@ lbm_status lbm_pool_add(lbm_pool *pool, lbm_lattice *lat, int64_t nsteps)
     s.flips = 0;
     s.t_target = nsteps;
     s.finishing = false;
+    s.tiles = own;
     lat->pool = pool;
     pool->dirty = true;
     if (nsteps == 0) {
@@ -902,6 +919,8 @@ lbm_status lbm_pool_set_shape(lbm_pool *pool, const lbm_pool_shape *shape)
     if (tiles > pool->max_tiles) return pfail(LBM_E_NOMEM, "shape needs %d tiles, pool has %d", tiles, pool->max_tiles);
     drop_graphs(pool);
     pool->shape = *shape;
+    for (Slot &s : pool->slots)
+        if (s.lat) s.tiles = tiles_of(*shape, s.lat);
     pool->dirty = true;
     return LBM_OK;
 }

@@ -3,14 +3,23 @@
 PyTorch supplies the device workspace and the stream; every operation is a
 call into the C ABI (``_lib``), which enqueues the library's own HIP kernels.
 """
+import contextlib
+
 import numpy as np
 import torch
 
 from . import _lib
 
+_NO_CONTEXT = contextlib.nullcontext()
+# handle of a device's current stream, without the Stream object that
+# torch.cuda.current_stream makes (5 us each)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 
 def _dev_f64(a, device):
     if isinstance(a, torch.Tensor):
+        if a.dtype == torch.float64 and a.device == device and a.is_contiguous():
+            return a
         t = a.to(device=device, dtype=torch.float64)
     else:
         t = torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to(device)
@@ -65,15 +74,31 @@ class Lattice:
     def handle(self):
         return self._h
 
+    def _is_current(self):
+        """Whether the lattice's stream is the current one of the current device."""
+        i = self.stream.device_index
+        return (_raw_stream is not None and torch.cuda.current_device() == i
+                and _raw_stream(i) == self.stream.cuda_stream)
+
+    def _on_stream(self):
+        """Context in which torch allocates on the lattice's stream; none where
+        that is current already (entering one costs 8 us, as much as a small
+        lattice's step)."""
+        return _NO_CONTEXT if self._is_current() else torch.cuda.stream(self.stream)
+
     # -- state ----------------------------------------------------------------
     def init(self, rho, ux, uy):
         """Equilibrium initialisation from [ny, nx] fields (numpy or torch)."""
         self._fields = [_dev_f64(a, self.device) for a in (rho, ux, uy)]
         for a in self._fields:
-            if tuple(a.shape) != (self.ny, self.nx):
+            if a.shape != (self.ny, self.nx):
                 raise ValueError(f"field shape {tuple(a.shape)} != {(self.ny, self.nx)}")
-            if self.stream != torch.cuda.current_stream(self.device):
-                self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        if self._is_current():
+            _lib.lbm_init_equilibrium(self._h, *(a.data_ptr() for a in self._fields))
+            return self
+        if self.stream != torch.cuda.current_stream(self.device):
+            self.stream.wait_stream(torch.cuda.current_stream(self.device))
+            for a in self._fields:
                 a.record_stream(self.stream)
         with torch.cuda.stream(self.stream):
             _lib.lbm_init_equilibrium(self._h, *(a.data_ptr() for a in self._fields))
@@ -93,7 +118,7 @@ class Lattice:
 
     def moments(self):
         """(rho, ux, uy) as [ny, nx] float64 device tensors (stream-ordered)."""
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             out = [torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device) for _ in range(3)]
             _lib.lbm_read_moments(self._h, *(a.data_ptr() for a in out))
         return tuple(out)
@@ -105,14 +130,14 @@ class Lattice:
     def project(self, mx, my, out=None):
         """Complex FP64 projection of the population deviations on mode (mx, my);
         returns (or fills) a float64 device tensor of 18 values."""
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             if out is None:
                 out = torch.empty(18, dtype=torch.float64, device=self.device)
             _lib.lbm_project(self._h, mx, my, out.data_ptr())
         return out
 
     def populations(self):
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             f = torch.empty((9, self.ny, self.nx), dtype=torch.float64, device=self.device)
             _lib.lbm_read_populations(self._h, f.data_ptr())
         return f
@@ -120,7 +145,7 @@ class Lattice:
     def set_populations(self, f):
         f = _dev_f64(f, self.device)
         self._fpop = f
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             _lib.lbm_write_populations(self._h, f.data_ptr())
         return self
 
@@ -130,14 +155,14 @@ class Lattice:
         return self
 
     def save_state(self):
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             buf = torch.empty(_lib.lbm_state_bytes(self._h), dtype=torch.uint8, device=self.device)
             _lib.lbm_save_state(self._h, buf.data_ptr())
         return buf, self.t
 
     def load_state(self, buf, t):
         self._loaded = buf
-        with torch.cuda.stream(self.stream):
+        with self._on_stream():
             _lib.lbm_load_state(self._h, buf.data_ptr(), t)
         return self
 

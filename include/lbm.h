@@ -109,8 +109,9 @@ typedef struct lbm_lattice lbm_lattice;
  * workgroups per compute unit cover the lattice in one round, at least 8:
  * 92, 69, 69, 137 rows on 4096^2); a smaller one with {0, 64, 4, 1, 1, 0}).
  * Until a shape is set by hand, lbm_step takes register tiles of its own
- * choice in its place on lattices of at most 3 * 2^21 cells: workgroups that
- * hold a tile of the lattice in registers for up to nine steps.
+ * choice in its place on lattices of up to 3.6 to 6.3 million cells (by
+ * storage type): workgroups that hold a tile of the lattice in registers for
+ * up to nine steps.
  *   variant   0 = one cell per lane (nine direct loads),
  *             1, 2, 3 = 2, 4, 8 consecutive cells per lane (aligned vector
  *             loads, x-shift by cross-lane exchange; needs nx % 2^variant == 0
@@ -365,10 +366,10 @@ typedef struct lbm_pool lbm_pool;
  *                two-wave strip (64 * 2 - 2(T-1) columns, rounded alike)
  *                go to one, run as a second launch beside the first.
  * The tile table holds the one-step tiles and, for T > 1, the strip tasks
- * of every unfinished member.  While the unfinished members hold few cells
- * (limits by storage type, 5 * 2^20 to 9 * 2^20) the shared-halo shapes (flags
- * 32, 34, 96, 98) take register tiles (see lbm_launch) in place of strips, as
- * far as the tile table has room for them. */
+ * of every unfinished member.  The shared-halo shapes (flags 32, 34, 96, 98)
+ * take register tiles (see lbm_launch) in place of strips where these leave
+ * the device or their lanes idle (few cells, narrow members), as far as the
+ * tile table has room for them; one workgroup each, whatever the grid. */
 typedef struct lbm_pool_shape {
     int32_t tile_cells;
     int32_t block;

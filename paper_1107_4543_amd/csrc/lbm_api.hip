@@ -163,16 +163,19 @@ lbm_launch default_launch(const View &v)
     return c;
 }
 
-// Register tiles in place of the default launch shape below kTileCells cells:
-// measured (us per step, strips -> tiles) FP32 2048^2 17.1 -> 13.4, 2600 x 2400
-// 22.8 -> 20.2, 4096^2 51.6 -> 51.6; FP16 2048^2 16.4 -> 14.0, 2600 x 2400
-// 20.6 -> 19.5, 4096^2 48.0 -> 51.8; FP64 2600 x 2400 40.9 -> 38.5, 4096^2 96
-// -> 108.
-constexpr int64_t kTileCells = (int64_t)3 << 21;
+// Register tiles in place of the default launch shape up to kTileCells cells,
+// by storage type.  Measured (us per step, strips -> tiles, a pulse on a field
+// at rest): FP32 1200 x 1000 6.6 -> 4.5, 2048^2 14.4 -> 12.6, 2600 x 2400 19.3 ->
+// 18.6; FP16 1500 x 1400 8.7 -> 7.7, 2048^2 13.1 -> 12.9, 2300 x 2200 15.0 -> 17.4;
+// BF16 2048^2 14.8 -> 13.3, 2300 x 2200 16.6 -> 17.7; FP64 2048 x 1500 19.5 ->
+// 17.9, 2048^2 25.4 -> 25.5, 2600 x 2400 35.2 -> 39.2.  (The clock follows the
+// power that the data cost: with noise in every cell the strips, which move
+// more through LDS and HBM, lose 15 %, the tiles 8 %.)
+constexpr int64_t kTileCells[4] = {(int64_t)7 << 19, (int64_t)3 << 21, (int64_t)1 << 22, (int64_t)1 << 22};
 
 lbm::TileShape default_tile(const View &v)
 {
-    if ((int64_t)v.nx * v.ny > kTileCells) return lbm::TileShape{};
+    if ((int64_t)v.nx * v.ny > kTileCells[v.storage]) return lbm::TileShape{};
     return lbm::tile_shape(v);
 }
 

@@ -53,7 +53,7 @@ struct TileShape {
 };
 bool tile_fits(const View &v);
 TileShape tile_shape(const View &v);
-TileShape tile_shape(const std::vector<const View *> &vs, int T);
+TileShape tile_shape(const std::vector<const View *> &vs, int T, double *us);
 void tile_output(const TileShape &t, int *cols, int *rows);
 hipError_t launch_tile(const View &v, const void *src, void *dst, const TileShape &t, int steps, hipStream_t st);
 // measure_only: compute max |g| (before scaling) into result[0], store nothing.

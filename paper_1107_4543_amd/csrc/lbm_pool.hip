@@ -202,15 +202,6 @@ int64_t tile_tasks(const lbm::TileShape &t, const View &v)
     return (int64_t)((v.nx + oc - 1) / oc) * ((v.ny + orow - 1) / orow);
 }
 
-// Most cells of a pool's unfinished members for register tiles, by storage
-// type.  Measured, us per step, strips -> tiles of the same T: FP32 one 64^2 4.5
-// -> 0.85, 40 of 64-200 (0.55M cells) 7.0 -> 3.4, 20 of 64-1024 (3.2M) 14.3 ->
-// 11.1, 60 of them (8.5M) 33.1 -> 28.8, four 1500^2 (9M) 29.7 -> 29.3, 256 of
-// 64-1024 (30M) 91 -> 120; FP64 60 of 64-1024 62.1 -> 57.8, four 1500^2 53.6 ->
-// 56.1; FP16 40 of 64-200 7.3 -> 4.0, 20 of 64-1024 12.3 -> 11.5, 60 of them 27.3
-// -> 28.8.
-constexpr int64_t kPoolTileCells[4] = {(int64_t)1 << 23, (int64_t)9 << 20, (int64_t)5 << 20, (int64_t)5 << 20};
-
 // Segment height of a pool's table: the shape's seg_rows, or -- when the
 // unfinished members' strips cut at that height give fewer tasks than fill
 // the device once (three four-wave workgroups per compute unit, the count a
@@ -269,26 +260,61 @@ int table_seg_rows(const lbm_pool *P)
     return fits(seg) ? seg : (fits(cap) ? cap : sh.seg_rows);
 }
 
+// Time of a T-step launch of the unfinished members on shared-halo strips, by
+// the work it holds: rows of 256 lanes, T-1 start-up rows' worth for every
+// segment, at the rate the strips ran at on 12 sets of members per storage type
+// (one 64^2 to 256 of 64-1024 and two of 3000^2; lane-updates per us): less while
+// the tasks fill one round of workgroups, more once a second round fills
+// the gaps the first leaves.  Few tasks: the rows follow one another.
+double strip_launch_us(const lbm_pool *P)
+{
+    static const double one_round[4] = {205e3, 400e3, 485e3, 485e3}, two_rounds[4] = {235e3, 500e3, 535e3, 535e3};
+    const lbm_pool_shape &sh = P->shape;
+    const int T = sh.steps_per_launch, seg = table_seg_rows(P);
+    double rows = 0, tasks = 0;
+    int storage = LBM_STORE_BF16;
+    for (const Slot &sl : P->slots) {
+        if (!sl.lat || sl.t_done >= sl.t_target) continue;
+        const int n = segments_of(seg, sl.lat), k = strips_of(sh, sl.lat);
+        rows += (double)k * (sl.lat->v.ny + (T - 1) * n);
+        tasks += (double)k * n;
+        storage = std::min(storage, sl.lat->v.storage);
+    }
+    const double fill = (double)lbm::device_cus() * (storage == LBM_STORE_F64 ? 2 : storage == LBM_STORE_F32 ? 3 : 4);
+    const double more = std::max(0.0, std::min(1.0, tasks / fill - 1.0));
+    const double rate = one_round[storage] + (two_rounds[storage] - one_round[storage]) * more;
+    const double chain = (seg + 2 * (T - 1)) * (storage == LBM_STORE_F64 ? 2.8 : 1.5);
+    return std::max(chain, rows * 64 * lbm::kWgMaxWaves * T / rate);
+}
+
 // Register tiles in place of strips for the unfinished members, or none: with
-// the shared-halo flags, while the members hold few cells (the least of the
-// limits of the storage types present) and the tile table has room for them.
+// the shared-halo flags, where the tiles' launch takes less time by the two
+// models (their choice is the faster one in 35 of those 36 sets, 1-3 % off in
+// the other), while the tile table has room for them.  Measured, us per step,
+// strips -> tiles of the same T: FP32 one 64^2 4.4 -> 0.82, 40 of 64-200 (0.55M
+// cells) 6.9 -> 3.3, 20 of 64-1024 (3.2M) 14.3 -> 10.7, 120 of them (11.6M) 49.5
+// -> 38.1, 256 (30M) 89.9 -> 102.5, four 1500^2 29.3 -> 28.9, two 3000^2 51.9 ->
+// 59.9; FP64 20 of 64-1024 24.5 -> 20.5, 120 of them 94.6 -> 73.9; FP16 40 of
+// 64-200 7.0 -> 3.6, 60 of 64-1024 27.1 -> 28.6.
 lbm::TileShape table_tile(const lbm_pool *P)
 {
     const lbm_pool_shape &sh = P->shape;
     lbm::TileShape t{};
     if (!wg_table(sh)) return t;
     std::vector<const View *> vs;
-    int64_t cells = 0, onestep = 0, most = INT64_MAX;
+    int64_t onestep = 0;
+    int storage = LBM_STORE_BF16;
     for (const Slot &sl : P->slots) {
         if (!sl.lat || sl.t_done >= sl.t_target) continue;
-        most = std::min(most, kPoolTileCells[sl.lat->v.storage]);
         vs.push_back(&sl.lat->v);
-        cells += (int64_t)sl.lat->v.nx * sl.lat->v.ny;
         onestep += onestep_tiles_of(sh, sl.lat);
+        storage = std::min(storage, sl.lat->v.storage);
     }
-    if (cells > most) return t;
-    t = lbm::tile_shape(vs, sh.steps_per_launch);
-    if (t.steps == 0) return t;
+    double us;
+    t = lbm::tile_shape(vs, sh.steps_per_launch, &us);
+    // the model, made for single lattices, is that much high for pools
+    us *= storage == LBM_STORE_F64 ? 0.9 : storage == LBM_STORE_F32 ? 1.0 : 0.93;
+    if (t.steps == 0 || us >= strip_launch_us(P)) return lbm::TileShape{};
     int64_t tasks = 0;
     for (const View *v : vs) tasks += tile_tasks(t, *v);
     return onestep + tasks <= P->max_tiles ? t : lbm::TileShape{};
@@ -397,7 +423,6 @@ lbm_status upload(lbm_pool *P)
                     t.t.x0 = x0;
                     t.t.nrows = y1 - y0;
                     t.t.ncols = std::min(oc, L->v.nx - x0);
-                    t.cells = t.t.nrows;
                     tasks.push_back(t);
                 }
             }
@@ -495,11 +520,13 @@ int launch_grid(const lbm_pool *P)
 // most the shape's grid.
 int multi_grid(const lbm_pool *P)
 {
-    const int per = wg_table(P->shape) || P->tile.steps ? 1 : P->shape.waves;
+    const int per = wg_table(P->shape) ? 1 : P->shape.waves;
     const int need = (P->max_range_tasks + per - 1) / per;
+    // tiles are short: a workgroup each, whatever the shape's grid
+    const int most = P->tile.steps ? 1 << 20 : P->shape.grid;
     int g = 1;
-    while (g < need && g < P->shape.grid) g *= 2;
-    return std::min(g, P->shape.grid);
+    while (g < need && g < most) g *= 2;
+    return std::min(g, most);
 }
 
 // Workgroups of a two-wave launch: one per task of the largest range,

@@ -20,7 +20,7 @@
 // took before (us per step): FP32 64^2 2.8 -> 0.71, 181 x 147 2.9 -> 0.80
 // (both one-step launches), 600 x 430 4.5 -> 1.5, 1000 x 760 5.9 -> 3.1, 2048^2
 // 17.1 -> 13.4 (strips); FP64 64^2 3.2 -> 0.92, 1500 x 1001 14.0 -> 9.8; BF16
-// 600 x 430 3.9 -> 1.7.
+// 600 x 430 3.9 -> 1.6.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -141,6 +141,14 @@ __device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, 
     W *const mine = (W *)lds + wv * (2 * 6 * kTileXch) + lane + 1;
     const W *const below = (W *)lds + (wv > 0 ? wv - 1 : 0) * (2 * 6 * kTileXch) + lane + 1;
     const W *const above = (W *)lds + (wv + 1 < nw ? wv + 1 : wv) * (2 * 6 * kTileXch) + lane + 1;
+    // With more than two rows per lane a wave at the tile's edge also skips
+    // the single rows that a step does not need, and the branch around each
+    // row keeps the compiler from interleaving the rows, whose conversions it
+    // otherwise holds in registers.  Us per step, all rows of a live wave |
+    // this: BF16 600 x 430 1.79 | 1.63, FP16 1500 x 1400 7.81 | 7.24, FP32 1536
+    // x 1024 5.50 | 5.37, FP64 600 x 430 2.50 | 2.44.  With one or two rows the
+    // branches cost a wave's chain more than they save (64^2 FP32 0.69 | 0.73).
+    constexpr bool ROWWISE = R > 2;
     auto update = [&](int j) {
         cell_update<S, C>(w[j], relax, scale, inv_scale);
         round_trip9<S>(w[j]);
@@ -150,8 +158,10 @@ __device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, 
         // step k is needed on tile rows k .. need - 1 - k
         const bool live = lo + R > k && lo < need - k;    // wave-uniform
         if (live) {
-            update(0);
-            if constexpr (R > 1) update(R - 1);
+            const int from = ROWWISE ? k - lo : 0, to = ROWWISE ? need - k - lo : R;
+            if (from <= 0 && to > 0) update(0);
+            if constexpr (R > 1)
+                if (from < R && to >= R) update(R - 1);
             mine[B + 0 * kTileXch] = w[R - 1][2];
             mine[B + 1 * kTileXch] = w[R - 1][5];
             mine[B + 2 * kTileXch] = w[R - 1][6];
@@ -159,7 +169,8 @@ __device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, 
             mine[B + 4 * kTileXch] = w[0][7];
             mine[B + 5 * kTileXch] = w[0][8];
 #pragma unroll
-            for (int j = 1; j < R - 1; ++j) update(j);
+            for (int j = 1; j < R - 1; ++j)
+                if (j >= from && j < to) update(j);
         }
         __syncthreads();
         if (live) {
@@ -353,13 +364,15 @@ double tile_us(int storage, const TileShape &t, const TileLoad &l)
 // type: more than four rows per lane leave too few waves in flight, fewer than
 // twelve waves too little tile for its halo.  Four rows: FP64 with eight waves
 // (with sixteen, one workgroup per compute unit is left), 16-bit with sixteen
-// (not in a pool, whose kernel then takes more than 64 registers, which halves
-// the waves in flight: 60 FP16 members of 8.5M cells 41 us per step).
+// (61-63 registers: two workgroups per compute unit; a pool of eight FP16
+// lattices of 128^2 to 1024^2 11.2 -> 9.0 us per step against three rows).
+// FP32 with four rows and sixteen waves is 7 % slower at 2048^2 and within 2 %
+// below.
 constexpr int32_t kTileShapes[][2] = {{1, 12}, {1, 16}, {2, 12}, {2, 16}, {3, 12}, {3, 16}, {4, 8}, {4, 16}};
-bool tile_shape_used(int storage, const int32_t s[2], bool pool)
+bool tile_shape_used(int storage, const int32_t s[2])
 {
     if (s[0] < 4) return true;
-    return s[1] == 8 ? storage == LBM_STORE_F64 : storage >= LBM_STORE_F16 && !pool;
+    return s[1] == 8 ? storage == LBM_STORE_F64 : storage >= LBM_STORE_F16;
 }
 
 }  // namespace
@@ -375,7 +388,7 @@ TileShape tile_shape(const View &v)
     double best_us = INFINITY;
     if (!tile_fits(v)) return best;
     for (const auto &s : kTileShapes) {
-        if (!tile_shape_used(v.storage, s, false)) continue;
+        if (!tile_shape_used(v.storage, s)) continue;
         for (int T = 2; T <= 9; ++T) {
             const TileShape t{s[0], s[1], T};
             TileLoad l;
@@ -402,7 +415,7 @@ TileShape tile_shape(const std::vector<const View *> &vs, int T, double *us_out)
         storage = std::min(storage, v->storage);
     }
     for (const auto &s : kTileShapes) {
-        if (!tile_shape_used(storage, s, true)) continue;
+        if (!tile_shape_used(storage, s)) continue;
         const TileShape t{s[0], s[1], T};
         TileLoad l;
         bool ok = !vs.empty();

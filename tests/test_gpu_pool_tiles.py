@@ -90,3 +90,13 @@ def test_timing_and_tuning_leave_tiled_members_as_they_are():
     assert pool.poll(wait=True) == [a]
     assert torch.equal(a.populations(), b.step(40).populations())
     pool.close()
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16"])
+def test_tall_16_bit_tiles_match_single_steps(storage):
+    # members large enough for the shape of four rows per lane and sixteen waves
+    from paper_1107_4543_amd.pool import Pool
+    pool = Pool(max_members=16, max_tiles=1 << 14)
+    pool.set_shape(tile_cells=512, block=256, graph_steps=28, steps_per_launch=6, flags=34)
+    run(pool, [(1024, 1000), (777, 1021), (53, 37), (901, 640)], [storage], [40, 23, 64, 31], 3)
+    pool.close()

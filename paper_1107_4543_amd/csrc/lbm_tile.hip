@@ -141,14 +141,15 @@ __device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, 
     W *const mine = (W *)lds + wv * (2 * 6 * kTileXch) + lane + 1;
     const W *const below = (W *)lds + (wv > 0 ? wv - 1 : 0) * (2 * 6 * kTileXch) + lane + 1;
     const W *const above = (W *)lds + (wv + 1 < nw ? wv + 1 : wv) * (2 * 6 * kTileXch) + lane + 1;
-    // With more than two rows per lane a wave at the tile's edge also skips
-    // the single rows that a step does not need, and the branch around each
-    // row keeps the compiler from interleaving the rows, whose conversions it
-    // otherwise holds in registers.  Us per step, all rows of a live wave |
-    // this: BF16 600 x 430 1.79 | 1.63, FP16 1500 x 1400 7.81 | 7.24, FP32 1536
-    // x 1024 5.50 | 5.37, FP64 600 x 430 2.50 | 2.44.  With one or two rows the
-    // branches cost a wave's chain more than they save (64^2 FP32 0.69 | 0.73).
-    constexpr bool ROWWISE = R > 2;
+    // With more than two rows per lane, or two in 16-bit storage, a wave at
+    // the tile's edge also skips the single rows that a step does not need, and
+    // the branch around each row keeps the compiler from interleaving the
+    // rows, whose conversions it otherwise holds in registers.  Us per step,
+    // all rows of a live wave | this: BF16 600 x 430 1.79 | 1.63, FP16 400 x 300
+    // 1.25 | 1.14, 1500 x 1400 7.81 | 7.24, FP32 1536 x 1024 5.50 | 5.37, FP64 600
+    // x 430 2.50 | 2.44.  Otherwise, with one or two rows, the branches cost a
+    // wave's chain more than they save (64^2 FP32 0.69 | 0.73).
+    constexpr bool ROWWISE = R > 2 || (R == 2 && Store<S>::scaled);
     auto update = [&](int j) {
         cell_update<S, C>(w[j], relax, scale, inv_scale);
         round_trip9<S>(w[j]);
@@ -309,16 +310,20 @@ hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const Ti
 
 // Launch time of a tile shape, from measurements of about 17 sizes from 37 x
 // 29 to 2600 x 2400 per storage type (6,000 launches each, residual 4 %; the
-// shape it picks is within 2-3 % of the best one on average).  t0: launch and
-// memory latency; row: one row of one wave, one step, on a SIMD of its own;
-// wg: load and store of one workgroup; bw: bytes per us to and from memory.
+// shape it picks is within 2-3 % of the best one on average).  The 16-bit rows
+// are 16 % below that fit, by what skipping single rows saved since (FP16 2048^2
+// then takes six steps per launch, 12.7 us per step, in place of four, 13.7;
+// pools of 120 lattices of 64^2 to 1024^2 tiles, 37.2, in place of strips, 39.5).
+// t0: launch and memory latency; row: one row of one wave, one step, on a SIMD
+// of its own; wg: load and store of one workgroup; bw: bytes per us to and from
+// memory.
 struct TileCost {
     double t0, row, wg, bw;
 };
 constexpr TileCost kTileCost[4] = {{1.99, 0.205, 1.70, 6.1e6},    // FP64
                                    {1.89, 0.110, 1.69, 5.1e6},    // FP32
-                                   {1.43, 0.139, 2.11, 3.75e6},   // FP16
-                                   {2.02, 0.134, 1.50, 3.75e6}};  // BF16
+                                   {1.43, 0.118, 2.11, 3.75e6},   // FP16
+                                   {2.02, 0.112, 1.50, 3.75e6}};  // BF16
 
 // What a launch of shape t on a lattice consists of: tiles, the wave-steps of
 // all of them, cells moved to and from memory.

@@ -39,7 +39,8 @@ def test_tiles_equal_single_steps(nx, ny, storage, compute):
         assert torch.equal(tiled.populations(), single.populations()), (n, tiled.t)
 
 
-@pytest.mark.parametrize("storage,nx,ny", [("f64", 2048, 1792), ("f32", 3072, 2048), ("f16", 2048, 2048), ("bf16", 2048, 2048)])
+@pytest.mark.parametrize("storage,nx,ny", [("f64", 2048, 1792), ("f32", 3072, 2048), ("f16", 2048, 2048), ("bf16", 2048, 2048),
+                                           ("bf16", 2560, 2048)])
 def test_largest_tiled_size_equals_single_steps(storage, nx, ny):
     # the storage type's most cells, and one row more (back to strips)
     for rows in (ny, ny + 1):

@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lbm_reduce.hpp"
 #include "lbm_step_common.hpp"
 
 namespace lbm {
@@ -937,8 +938,7 @@ struct ProjectF {
     {
         const CellArgs a = make_cell_args(v);
         const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
-        const auto mod = [](int32_t k, int32_t n) { return (k % n + n) % n; };
-        const Mode m{mod(mx, v.nx), mod(my, v.ny), v.nx, v.ny, v.inv_scale};
+        const Mode m{wrap_mode(mx, v.nx), wrap_mode(my, v.ny), v.nx, v.ny, v.inv_scale};
         const bool wide = red_wide(v);
         const RedShape g = red_shape(v, wide ? 1024 : 256);
         if (wide) hipLaunchKernelGGL((k_project<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, m, partials, out);

@@ -1,0 +1,40 @@
+"""Index arithmetic of the global reductions (csrc/lbm_reduce.hpp) at the
+largest lattices that lbm_create takes, compiled with the host compiler:
+evaluated in constant expressions, where an overflow is a compile error, and
+against 128-bit arithmetic."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1107_4543_amd", "csrc")
+# the largest width (pitch a multiple of 64, pitch * ny < 2^31)
+WIDEST = 2 ** 31 - 64
+
+
+def check(tmp_path, body, asserts=()):
+    src = os.path.join(str(tmp_path), "t.cpp")
+    with open(src, "w") as fh:
+        fh.write('#include <cstdio>\n#include "lbm_reduce.hpp"\nusing namespace lbm;\ntypedef __int128 wide;\n')
+        for a in asserts:
+            fh.write(f'static_assert({a}, "");\n')
+        fh.write("int main()\n{\n" + body + "\n    return 0;\n}\n")
+    exe = src[:-4]
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-ftrapv", "-Wall", "-I", CSRC, src, "-o", exe], capture_output=True,
+                       text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, (r.returncode, r.stdout[-2000:])
+
+
+def test_modes_of_very_wide_lattices(tmp_path):
+    check(tmp_path, """
+    const int ks[] = {0, 1, -1, 12345, -70001, 1500000000, -1500000000, 2147483647, -2147483647 - 1};
+    const int ns[] = {1, 2, 3, 64, 65535, 1 << 30, (1 << 30) + 1, 1600000000, %d};
+    for (int n : ns)
+        for (int k : ks) {
+            wide want = (wide)k %% n;
+            if (want < 0) want += n;
+            if (wrap_mode(k, n) != want) { printf("%%d mod %%d: %%d", k, n, wrap_mode(k, n)); return 1; }
+        }""" % WIDEST, ["wrap_mode(1500000000, 1600000000) == 1500000000", f"wrap_mode(-1, {WIDEST}) == {WIDEST - 1}"])

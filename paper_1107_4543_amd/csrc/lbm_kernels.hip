@@ -639,35 +639,11 @@ __global__ void __launch_bounds__(256) k_write_pop(CellArgs a, const double *f, 
     }
 }
 
-// Cells of the lattice that a block of a reduction takes: block b has the
-// columns [cols (b mod bx), ...) and every by-th band of h rows, h = threads >>
-// shift, from band b / bx on.  Its threads lie in rows of 2^shift (at least the
-// lattice's width where that is less than the block's), so that a thread
-// keeps its column.  Neighbouring bands go to neighbouring blocks, so that the
-// device sweeps through memory as one front: with a stretch of rows of its own
-// for each block, 4096^2 FP32 diagnostics took 166 us instead of 110.
-struct RedShape {
-    int32_t bx, by, cols, shift;
-    __host__ __device__ int blocks() const { return bx * by; }
-};
-
-RedShape red_shape(const View &v, int threads)
-{
-    RedShape g;
-    g.shift = 0;
-    while ((1 << g.shift) < threads && (1 << g.shift) < v.nx) ++g.shift;
-    const int w = 1 << g.shift, h = threads >> g.shift;
-    const int tx = (v.nx + w - 1) / w;
-    g.cols = w * ((tx + kRedBlocks - 1) / kRedBlocks);
-    g.bx = (v.nx + g.cols - 1) / g.cols;
-    // at least two cells per thread
-    g.by = std::max(1, std::min(kRedBlocks / g.bx, (v.ny + 2 * h - 1) / (2 * h)));
-    return g;
-}
-
 // Threads per block of a reduction: 1024 where 512 blocks of 256 would leave
 // a thread more than eight cells.
 bool red_wide(const View &v) { return (int64_t)v.nx * v.ny > (int64_t)kRedBlocks * 256 * 8; }
+
+RedShape red_shape(const View &v, bool wide) { return red_shape(v.nx, v.ny, wide ? 1024 : 256, kRedBlocks); }
 
 // Global sums of the collision invariants (aligned reads: a global sum does
 // not need the pull shift) and the count of non-finite stored values.
@@ -677,9 +653,10 @@ __global__ void __launch_bounds__(BT) k_diag(CellArgs a, RedShape g, const typen
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     __shared__ double red[4];
     const int by = (int)blockIdx.x / g.bx, bx = (int)blockIdx.x - by * g.bx;
-    const int x0 = bx * g.cols, x1 = min(a.nx, x0 + g.cols);
-    const int w = 1 << g.shift, h = BT >> g.shift;
-    for (int x = x0 + ((int)threadIdx.x & (w - 1)); x < x1; x += w)
+    const RedCols cols = red_cols(g, bx, a.nx);
+    const uint32_t w = 1u << g.shift;
+    const int h = BT >> g.shift;
+    for (uint32_t x = cols.from + (threadIdx.x & (w - 1)); x < cols.to; x += w)
 #pragma unroll 2
         for (int y = by * h + ((int)threadIdx.x >> g.shift); y < a.ny; y += g.by * h) {
             const typename Store<S>::raw *p = src + ((int64_t)y * a.pitch + x);
@@ -747,8 +724,9 @@ __global__ void __launch_bounds__(BT) k_project(CellArgs a, RedShape g, const ty
     for (int k = 0; k < 18; ++k) acc[k] = 0.0;
     __shared__ double ec[256], es[256], red[18];
     const int by = (int)blockIdx.x / g.bx, bx = (int)blockIdx.x - by * g.bx;
-    const int x0 = bx * g.cols, x1 = min(a.nx, x0 + g.cols);
-    const int w = 1 << g.shift, hs = __ffs(BT >> g.shift) - 1, h = 1 << hs;
+    const RedCols cols = red_cols(g, bx, a.nx);
+    const uint32_t w = 1u << g.shift;
+    const int hs = __ffs(BT >> g.shift) - 1, h = 1 << hs;
     // the block's rows by their order in it
     const int first = by << hs, band = g.by << hs;
     const int bands = first < a.ny ? (a.ny - first + band - 1) / band : 0;
@@ -757,9 +735,9 @@ __global__ void __launch_bounds__(BT) k_project(CellArgs a, RedShape g, const ty
         const auto row = [&](int q) { return first + ((q0 + q) >> hs) * band + ((q0 + q) & (h - 1)); };
         if ((int)threadIdx.x < n) phase(m.my, min(row((int)threadIdx.x), a.ny - 1), a.ny, &ec[threadIdx.x], &es[threadIdx.x]);
         __syncthreads();
-        for (int x = x0 + ((int)threadIdx.x & (w - 1)); x < x1; x += w) {
+        for (uint32_t x = cols.from + (threadIdx.x & (w - 1)); x < cols.to; x += w) {
             double cx, sx;
-            phase(m.mx, x, a.nx, &cx, &sx);
+            phase(m.mx, (int)x, a.nx, &cx, &sx);
 #pragma unroll 2
             for (int q = (int)threadIdx.x >> g.shift; q < n; q += h) {
                 const int y = row(q);
@@ -922,7 +900,7 @@ struct DiagF {
     {
         const CellArgs a = make_cell_args(v);
         const bool wide = red_wide(v);
-        const RedShape g = red_shape(v, wide ? 1024 : 256);
+        const RedShape g = red_shape(v, wide);
         const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
         if (wide) hipLaunchKernelGGL((k_diag<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, partials);
         else hipLaunchKernelGGL((k_diag<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, partials);
@@ -940,7 +918,7 @@ struct ProjectF {
         const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
         const Mode m{wrap_mode(mx, v.nx), wrap_mode(my, v.ny), v.nx, v.ny, v.inv_scale};
         const bool wide = red_wide(v);
-        const RedShape g = red_shape(v, wide ? 1024 : 256);
+        const RedShape g = red_shape(v, wide);
         if (wide) hipLaunchKernelGGL((k_project<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, m, partials, out);
         else hipLaunchKernelGGL((k_project<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, m, partials, out);
         // a lattice of one block has its result already

@@ -16,7 +16,7 @@ WIDEST = 2 ** 31 - 64
 def check(tmp_path, body, asserts=()):
     src = os.path.join(str(tmp_path), "t.cpp")
     with open(src, "w") as fh:
-        fh.write('#include <cstdio>\n#include "lbm_reduce.hpp"\nusing namespace lbm;\ntypedef __int128 wide;\n')
+        fh.write('#include <cstdio>\n#include <initializer_list>\n#include "lbm_reduce.hpp"\nusing namespace lbm;\ntypedef __int128 wide;\n')
         for a in asserts:
             fh.write(f'static_assert({a}, "");\n')
         fh.write("int main()\n{\n" + body + "\n    return 0;\n}\n")
@@ -38,3 +38,30 @@ def test_modes_of_very_wide_lattices(tmp_path):
             if (want < 0) want += n;
             if (wrap_mode(k, n) != want) { printf("%%d mod %%d: %%d", k, n, wrap_mode(k, n)); return 1; }
         }""" % WIDEST, ["wrap_mode(1500000000, 1600000000) == 1500000000", f"wrap_mode(-1, {WIDEST}) == {WIDEST - 1}"])
+
+
+def test_blocks_share_out_every_column_and_band_once(tmp_path):
+    # widths around a block's threads and up to the widest lattice; bands are
+    # counted for the tallest lattice of the width, and for few rows
+    check(tmp_path, """
+    const int ns[] = {1, 2, 3, 255, 256, 257, 1023, 1025, 40000, 524287, 524289, (1 << 30) + 1, 1600000000, 2143400000, %d};
+    for (int threads : {256, 1024})
+        for (int nx : ns)
+            for (int rows = 0; rows < 4; ++rows) {
+                const wide pitch = ((wide)nx + 63) / 64 * 64;
+                const int tallest = (int)((((wide)1 << 31) - 1) / pitch);
+                const int ny = rows == 3 ? tallest : rows + 1 < tallest ? rows + 1 : tallest;
+                const RedShape g = red_shape(nx, ny, threads, 512);
+                const int w = 1 << g.shift, h = threads >> g.shift;
+                printf("%%d x %%d, %%d threads: bx %%d by %%d cols %%d shift %%d\\n", nx, ny, threads, g.bx, g.by, g.cols, g.shift);
+                if (g.bx < 1 || g.by < 1 || g.blocks() > 512 || g.cols < 1 || g.cols %% w || w * h != threads) return 1;
+                wide at = 0;
+                for (int b = 0; b < g.bx; ++b) {
+                    const RedCols c = red_cols(g, b, nx);
+                    if (c.from != at || c.to <= c.from || c.to > (uint32_t)nx) return 2;
+                    // the last column of the last thread, and the one after it that ends its loop
+                    if ((uint32_t)(c.to - 1 + w) < c.to) return 3;
+                    at = c.to;
+                }
+                if (at != nx) return 4;
+            }""" % WIDEST, [f"red_shape({WIDEST}, 1, 1024, 512).bx == 512", "red_shape(2143400000, 1, 1024, 512).bx > 0"])

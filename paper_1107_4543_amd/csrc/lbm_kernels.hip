@@ -683,13 +683,7 @@ __global__ void __launch_bounds__(BT) k_diag(CellArgs a, RedShape g, const typen
 // 0 <= m < n, -1 <= v < n.
 __device__ __forceinline__ void phase(int m, int v, int n, double *cs, double *sn)
 {
-    double p;
-    if (n <= 0xffff) {                                  // m v fits 32 bits
-        p = (double)((uint32_t)(m * (v < 0 ? v + n : v)) % (uint32_t)n);
-    } else {
-        int64_t q = ((int64_t)m * v) % n;
-        p = (double)(q < 0 ? q + n : q);
-    }
+    const double p = (double)phase_index(m, v, n);
     sincospi(2.0 * (p / n), sn, cs);
 }
 

@@ -17,6 +17,16 @@ constexpr int32_t wrap_mode(int32_t k, int32_t n)
     return r < 0 ? r + n : r;
 }
 
+// (m v) mod n for a mode 0 <= m < n and a coordinate -1 <= v < n.  Up to 65535
+// the product fits 32 unsigned bits (not 31: 65534 * 65534), and the remainder
+// costs a 32-bit division instead of a 64-bit one.
+constexpr uint32_t phase_index(int32_t m, int32_t v, int32_t n)
+{
+    const uint32_t w = (uint32_t)(v < 0 ? v + n : v);
+    if (n <= 0xffff) return (uint32_t)m * w % (uint32_t)n;
+    return (uint32_t)((uint64_t)m * w % (uint32_t)n);
+}
+
 // Cells of the lattice that a block of a reduction takes: block b has the
 // columns [cols (b mod bx), ...) and every by-th band of h rows, h = threads >>
 // shift, from band b / bx on.  Its threads lie in rows of 2^shift (at least the

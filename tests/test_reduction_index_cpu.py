@@ -65,3 +65,17 @@ def test_blocks_share_out_every_column_and_band_once(tmp_path):
                 }
                 if (at != nx) return 4;
             }""" % WIDEST, [f"red_shape({WIDEST}, 1, 1024, 512).bx == 512", "red_shape(2143400000, 1, 1024, 512).bx > 0"])
+
+
+def test_phase_products_up_to_the_edges_of_the_32_bit_path(tmp_path):
+    check(tmp_path, """
+    const int ns[] = {1, 2, 46341, 46342, 60000, 65535, 65536, 65537, 1 << 20, 1600000000, %d};
+    for (int n : ns)
+        for (int m : {0, 1, n / 2, n - 2, n - 1})
+            for (int v : {-1, 0, 1, n / 2, n - 2, n - 1}) {
+                if (m < 0 || m >= n || v >= n) continue;
+                wide want = (wide)m * v %% n;
+                if (want < 0) want += n;
+                if (phase_index(m, v, n) != want) { printf("%%d * %%d mod %%d: %%u", m, v, n, phase_index(m, v, n)); return 1; }
+            }""" % WIDEST, ["phase_index(65534, 65534, 65535) == 1", "phase_index(46341, 46341, 46342) == 1",
+                            "phase_index(65534, -1, 65535) == 1"])

@@ -643,7 +643,7 @@ __global__ void __launch_bounds__(256) k_write_pop(CellArgs a, const double *f, 
 // a thread more than eight cells.
 bool red_wide(const View &v) { return (int64_t)v.nx * v.ny > (int64_t)kRedBlocks * 256 * 8; }
 
-RedShape red_shape(const View &v, bool wide) { return red_shape(v.nx, v.ny, wide ? 1024 : 256, kRedBlocks); }
+RedShape red_split(const View &v, bool wide) { return red_shape(v.nx, v.ny, wide ? 1024 : 256, kRedBlocks); }
 
 // Global sums of the collision invariants (aligned reads: a global sum does
 // not need the pull shift) and the count of non-finite stored values.
@@ -894,7 +894,7 @@ struct DiagF {
     {
         const CellArgs a = make_cell_args(v);
         const bool wide = red_wide(v);
-        const RedShape g = red_shape(v, wide);
+        const RedShape g = red_split(v, wide);
         const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
         if (wide) hipLaunchKernelGGL((k_diag<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, partials);
         else hipLaunchKernelGGL((k_diag<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, partials);
@@ -912,7 +912,7 @@ struct ProjectF {
         const typename Store<S>::raw *p = (const typename Store<S>::raw *)src;
         const Mode m{wrap_mode(mx, v.nx), wrap_mode(my, v.ny), v.nx, v.ny, v.inv_scale};
         const bool wide = red_wide(v);
-        const RedShape g = red_shape(v, wide);
+        const RedShape g = red_split(v, wide);
         if (wide) hipLaunchKernelGGL((k_project<S, 1024>), dim3(g.blocks()), dim3(1024), 0, st, a, g, p, m, partials, out);
         else hipLaunchKernelGGL((k_project<S, 256>), dim3(g.blocks()), dim3(256), 0, st, a, g, p, m, partials, out);
         // a lattice of one block has its result already

@@ -298,9 +298,10 @@ LBM_API lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg);
 /* Times the supported launch shapes on this lattice (reps launches each,
  * the state is left unchanged) and selects the one with the least time per
  * step; the fastest one-step shape is kept for a single left-over step
- * (see lbm_step for the rest).  Register tiles stay in use where they take
- * less time per step than the selected shape.  best_us
- * receives microseconds per step.  best/best_us may be NULL.  Syncs. */
+ * (see lbm_step for the rest).  best receives that shape and best_us its
+ * microseconds per step; either may be NULL.  Register tiles stay in use in
+ * the shape's place where they take less time per step still; setting best
+ * by hand then takes them out and steps at best_us.  Syncs. */
 LBM_API lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *best_us);
 /* Times n launches of the current shape (state unchanged; syncs); avg_us is
  * per launch, which covers lbm_steps_per_launch steps. */

@@ -718,8 +718,7 @@ lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *be
     }
     std::sort(fin.begin(), fin.end(), [](const Timed &a, const Timed &b) { return a.us < b.us; });
     // the register tiles that a lattice of this size starts with stay in use
-    // where they are faster still
-    double us = fin.front().us;
+    // where they are faster still; best and best_us stay one shape's
     lbm::TileShape tile = default_tile(lat->v);
     if (tile.steps > 1) {
         double t = INFINITY;
@@ -731,14 +730,13 @@ lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *be
             if (st != LBM_OK) return st;
             t = std::min(t, once / tile.steps);
         }
-        if (t < us) us = t;
-        else tile = lbm::TileShape{};
+        if (t >= fin.front().us) tile = lbm::TileShape{};
     }
     lat->launch = fin.front().c;
     lat->single = best_single;
     lat->tile = tile;
     if (best) *best = fin.front().c;
-    if (best_us) *best_us = us;
+    if (best_us) *best_us = fin.front().us;
     return LBM_OK;
 }
 

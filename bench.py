@@ -360,7 +360,7 @@ def run_batch256(steps, pool_shape=None, sequential=True):
         equal = all(torch.equal(r, lat.moments()[0]) for r, lat in zip(batched_rho, lats))
     pool.close()
     return {"ms_batched": ms_batched, "ms_seq": ms_seq, "equal": equal, "shape": shape, "cells": cells,
-            "lattices": len(specs), "draws": draws[0], "seq_launch": lats[0].launch, "seed": w["seed"]}
+            "lattices": len(specs), "draws": draws[0], "seq_launch": lats[0].tiles or lats[0].launch, "seed": w["seed"]}
 
 
 def batch_summary(r, steps):

@@ -165,6 +165,15 @@ typedef struct lbm_launch {
     int32_t flags;
 } lbm_launch;
 
+/* Register tiles of a lattice: `waves` waves per workgroup, `rows` rows per
+ * lane, up to `steps` steps per launch.  All 0: lbm_step takes the launch
+ * shape. */
+typedef struct lbm_tiles {
+    int32_t rows;
+    int32_t waves;
+    int32_t steps;
+} lbm_tiles;
+
 /* ---- status and helpers ------------------------------------------------ */
 
 /* Static text for a status code; never NULL. */
@@ -291,10 +300,16 @@ LBM_API lbm_status lbm_load_state(lbm_lattice *lat, const void *dev_src, int64_t
 /* Steps taken since init (or the t given to lbm_load_state). */
 LBM_API int64_t lbm_time(const lbm_lattice *lat);
 
-/* Launch shape of the step kernel for this lattice. */
+/* Launch shape of the step kernel for this lattice.  While register tiles
+ * are in use (lbm_get_tiles) they take its place in every lbm_step of more
+ * than one step. */
 LBM_API lbm_status lbm_get_launch(const lbm_lattice *lat, lbm_launch *out);
-/* LBM_E_INVAL if the shape is not supported for this lattice. */
+/* Sets the launch shape and takes register tiles out of use, also with the
+ * shape that lbm_get_launch returned.  LBM_E_INVAL if the shape is not
+ * supported for this lattice. */
 LBM_API lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg);
+/* The register tiles in use, or all 0. */
+LBM_API lbm_status lbm_get_tiles(const lbm_lattice *lat, lbm_tiles *out);
 /* Times the supported launch shapes on this lattice (reps launches each,
  * the state is left unchanged) and selects the one with the least time per
  * step; the fastest one-step shape is kept for a single left-over step
@@ -303,8 +318,9 @@ LBM_API lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg);
  * the shape's place where they take less time per step still; setting best
  * by hand then takes them out and steps at best_us.  Syncs. */
 LBM_API lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *best_us);
-/* Times n launches of the current shape (state unchanged; syncs); avg_us is
- * per launch, which covers lbm_steps_per_launch steps. */
+/* Times n launches of what an lbm_step of many steps takes (state unchanged;
+ * syncs): of the register tiles in use, each of lbm_tiles.steps steps, else of
+ * the launch shape, each of lbm_steps_per_launch steps; avg_us per launch. */
 LBM_API lbm_status lbm_time_launches(lbm_lattice *lat, int32_t n, double *avg_us);
 /* Steps one launch of this shape advances (1, or T for variants 8-13);
  * 0 if cfg is NULL.  Does not validate the shape. */

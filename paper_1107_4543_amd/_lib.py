@@ -48,6 +48,13 @@ class lbm_launch(ctypes.Structure):
         return {k: int(getattr(self, k)) for k, _ in self._fields_}
 
 
+class lbm_tiles(ctypes.Structure):
+    _fields_ = [("rows", ctypes.c_int32), ("waves", ctypes.c_int32), ("steps", ctypes.c_int32)]
+
+    def as_dict(self):
+        return {k: int(getattr(self, k)) for k, _ in self._fields_}
+
+
 class lbm_pool_shape(ctypes.Structure):
     _fields_ = [("tile_cells", ctypes.c_int32), ("block", ctypes.c_int32),
                 ("grid", ctypes.c_int32), ("graph_steps", ctypes.c_int32),
@@ -89,6 +96,7 @@ SIGNATURES = {
     "lbm_time": (ctypes.c_int64, [_vp]),
     "lbm_get_launch": (_st, [_vp, ctypes.POINTER(lbm_launch)]),
     "lbm_set_launch": (_st, [_vp, ctypes.POINTER(lbm_launch)]),
+    "lbm_get_tiles": (_st, [_vp, ctypes.POINTER(lbm_tiles)]),
     "lbm_tune": (_st, [_vp, ctypes.c_int32, ctypes.POINTER(lbm_launch), _dp]),
     "lbm_time_launches": (_st, [_vp, ctypes.c_int32, _dp]),
     "lbm_steps_per_launch": (ctypes.c_int32, [ctypes.c_void_p]),
@@ -241,6 +249,12 @@ def lbm_get_launch(h):
 
 def lbm_set_launch(h, cfg):
     check(load().lbm_set_launch(h, ctypes.byref(cfg)), "lbm_set_launch")
+
+
+def lbm_get_tiles(h):
+    t = lbm_tiles()
+    check(load().lbm_get_tiles(h, ctypes.byref(t)), "lbm_get_tiles")
+    return t
 
 
 def lbm_tune(h, reps):

@@ -287,6 +287,12 @@ lbm_status time_shape(lbm_lattice *L, const lbm_launch &c, int reps, double *us)
     return time_launch(L, reps, us, [&](const void *src, void *dst) { return lbm::launch_step(L->v, src, dst, c, L->stream); });
 }
 
+lbm_status time_tile(lbm_lattice *L, const lbm::TileShape &t, int reps, double *us)
+{
+    return time_launch(L, reps, us,
+                       [&](const void *src, void *dst) { return lbm::launch_tile(L->v, src, dst, t, t.steps, L->stream); });
+}
+
 }  // namespace
 
 void lbm::set_error_text(const char *msg) { g_err = msg; }
@@ -648,6 +654,13 @@ lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg)
     return LBM_OK;
 }
 
+lbm_status lbm_get_tiles(const lbm_lattice *lat, lbm_tiles *out)
+{
+    if (!lat || !out) return fail(LBM_E_INVAL, "NULL argument");
+    *out = lbm_tiles{lat->tile.rows, lat->tile.waves, lat->tile.steps};
+    return LBM_OK;
+}
+
 int32_t lbm_steps_per_launch(const lbm_launch *cfg) { return cfg ? lbm::steps_per_launch(*cfg) : 0; }
 
 lbm_status lbm_time_launches(lbm_lattice *lat, int32_t n, double *avg_us)
@@ -655,7 +668,7 @@ lbm_status lbm_time_launches(lbm_lattice *lat, int32_t n, double *avg_us)
     if (!lat || !avg_us || n < 1) return fail(LBM_E_INVAL, "bad argument");
     if (!lat->initialized) return fail(LBM_E_STATE, "time before init");
     if (lat->pool) return busy(lat);
-    return time_shape(lat, lat->launch, n, avg_us);
+    return lat->tile.steps ? time_tile(lat, lat->tile, n, avg_us) : time_shape(lat, lat->launch, n, avg_us);
 }
 
 lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *best_us)
@@ -724,10 +737,7 @@ lbm_status lbm_tune(lbm_lattice *lat, int32_t reps, lbm_launch *best, double *be
         double t = INFINITY;
         for (int k = 0; k < 2; ++k) {
             double once;
-            st = time_launch(lat, 4 * reps, &once, [&](const void *src, void *dst) {
-                return lbm::launch_tile(lat->v, src, dst, tile, tile.steps, lat->stream);
-            });
-            if (st != LBM_OK) return st;
+            if ((st = time_tile(lat, tile, 4 * reps, &once)) != LBM_OK) return st;
             t = std::min(t, once / tile.steps);
         }
         if (t >= fin.front().us) tile = lbm::TileShape{};

@@ -169,6 +169,8 @@ class Lattice:
     # -- launch shape -----------------------------------------------------------
     @property
     def launch(self):
+        """The launch shape; `tiles`, where in use, take its place in every
+        step(n) of more than one step, until set_launch."""
         return _lib.lbm_get_launch(self._h).as_dict()
 
     def set_launch(self, variant=0, block_x=64, block_y=4, rows=1, xcd_remap=1, flags=0):
@@ -177,9 +179,17 @@ class Lattice:
         return self
 
     @property
+    def tiles(self):
+        """The register tiles that step() takes in the launch shape's place
+        (rows per lane, waves per workgroup, most steps per launch), or None."""
+        t = _lib.lbm_get_tiles(self._h)
+        return t.as_dict() if t.steps else None
+
+    @property
     def steps_per_launch(self):
-        """Steps one launch of the current shape advances."""
-        return _lib.lbm_steps_per_launch(_lib.lbm_get_launch(self._h))
+        """Steps that one launch of a long step() advances: the register tiles'
+        where these are in use, else the launch shape's."""
+        return _lib.lbm_get_tiles(self._h).steps or _lib.lbm_steps_per_launch(_lib.lbm_get_launch(self._h))
 
     def launches_for(self, n):
         """Kernel launches step(n) makes with the current shapes."""
@@ -193,5 +203,5 @@ class Lattice:
         return c.as_dict(), us
 
     def time_launches(self, n):
-        """Microseconds per launch of the current shape (steps_per_launch steps)."""
+        """Microseconds per launch of a long step() (steps_per_launch steps)."""
         return _lib.lbm_time_launches(self._h, n)

@@ -305,11 +305,14 @@ LBM_API int64_t lbm_time(const lbm_lattice *lat);
  * than one step. */
 LBM_API lbm_status lbm_get_launch(const lbm_lattice *lat, lbm_launch *out);
 /* Sets the launch shape and takes register tiles out of use, also with the
- * shape that lbm_get_launch returned.  LBM_E_INVAL if the shape is not
+ * shape that lbm_get_launch returned (lbm_set_tiles brings them back).  LBM_E_INVAL if the shape is not
  * supported for this lattice. */
 LBM_API lbm_status lbm_set_launch(lbm_lattice *lat, const lbm_launch *cfg);
 /* The register tiles in use, or all 0. */
 LBM_API lbm_status lbm_get_tiles(const lbm_lattice *lat, lbm_tiles *out);
+/* on != 0: the register tiles that a new lattice of this size starts with (if
+ * any) into use again, beside the launch shape as it is; 0: out of use. */
+LBM_API lbm_status lbm_set_tiles(lbm_lattice *lat, int32_t on);
 /* Times the supported launch shapes on this lattice (reps launches each,
  * the state is left unchanged) and selects the one with the least time per
  * step; the fastest one-step shape is kept for a single left-over step

@@ -97,6 +97,7 @@ SIGNATURES = {
     "lbm_get_launch": (_st, [_vp, ctypes.POINTER(lbm_launch)]),
     "lbm_set_launch": (_st, [_vp, ctypes.POINTER(lbm_launch)]),
     "lbm_get_tiles": (_st, [_vp, ctypes.POINTER(lbm_tiles)]),
+    "lbm_set_tiles": (_st, [_vp, ctypes.c_int32]),
     "lbm_tune": (_st, [_vp, ctypes.c_int32, ctypes.POINTER(lbm_launch), _dp]),
     "lbm_time_launches": (_st, [_vp, ctypes.c_int32, _dp]),
     "lbm_steps_per_launch": (ctypes.c_int32, [ctypes.c_void_p]),
@@ -255,6 +256,10 @@ def lbm_get_tiles(h):
     t = lbm_tiles()
     check(load().lbm_get_tiles(h, ctypes.byref(t)), "lbm_get_tiles")
     return t
+
+
+def lbm_set_tiles(h, on):
+    check(load().lbm_set_tiles(h, 1 if on else 0), "lbm_set_tiles")
 
 
 def lbm_tune(h, reps):

@@ -661,6 +661,13 @@ lbm_status lbm_get_tiles(const lbm_lattice *lat, lbm_tiles *out)
     return LBM_OK;
 }
 
+lbm_status lbm_set_tiles(lbm_lattice *lat, int32_t on)
+{
+    if (!lat) return fail(LBM_E_INVAL, "lattice is NULL");
+    lat->tile = on ? default_tile(lat->v) : lbm::TileShape{};
+    return LBM_OK;
+}
+
 int32_t lbm_steps_per_launch(const lbm_launch *cfg) { return cfg ? lbm::steps_per_launch(*cfg) : 0; }
 
 lbm_status lbm_time_launches(lbm_lattice *lat, int32_t n, double *avg_us)

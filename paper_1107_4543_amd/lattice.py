@@ -185,6 +185,12 @@ class Lattice:
         t = _lib.lbm_get_tiles(self._h)
         return t.as_dict() if t.steps else None
 
+    def set_tiles(self, on=True):
+        """The register tiles of a lattice of this size into use again after
+        set_launch, or out of use."""
+        _lib.lbm_set_tiles(self._h, on)
+        return self
+
     @property
     def steps_per_launch(self):
         """Steps that one launch of a long step() advances: the register tiles'

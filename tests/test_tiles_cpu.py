@@ -35,3 +35,21 @@ def test_reported_tiles_are_those_of_the_launch_count(nx, ny, storage):
         assert _lib.lbm_get_tiles(h).steps == 0
     finally:
         _lib.lbm_destroy(h)
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (4096, 4096)])
+def test_a_saved_shape_can_be_restored_with_its_tiles(nx, ny):
+    h = create(nx, ny, "f32")
+    try:
+        shape, tiles = _lib.lbm_get_launch(h).as_dict(), _lib.lbm_get_tiles(h).as_dict()
+        n = _lib.lbm_step_launches(h, 100)
+        _lib.lbm_set_launch(h, _lib.lbm_launch(0, 64, 4, 1, 1, 0))
+        assert _lib.lbm_step_launches(h, 100) == 100
+        _lib.lbm_set_launch(h, _lib.lbm_launch(*shape.values()))
+        _lib.lbm_set_tiles(h, tiles["steps"] > 0)
+        assert _lib.lbm_get_launch(h).as_dict() == shape and _lib.lbm_get_tiles(h).as_dict() == tiles
+        assert _lib.lbm_step_launches(h, 100) == n
+        _lib.lbm_set_tiles(h, False)
+        assert _lib.lbm_get_tiles(h).steps == 0
+    finally:
+        _lib.lbm_destroy(h)

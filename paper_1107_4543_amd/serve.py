@@ -245,15 +245,14 @@ class Server:
     that separate pools by lattice size (ascending; the default () puts
     every job in one pool, which measured the higher aggregate rate and the
     lower mean latency under load; classes gave the lower median).
-    gather_ms: without solo, a job that finds the server empty waits this
-    long for others to share its launches with (a job of 64^2 cells and 200
-    steps takes 0.6 ms in the pool, less than a batch takes to come together
-    at 1000 jobs/s); with solo it starts at once on its own."""
+    gather_ms: without solo, a job that finds the server empty waits up to
+    this long for others to share its launches with; 0 (the default) starts
+    it at once, as solo always does."""
 
     def __init__(self, hbm_budget_bytes, max_members=256, max_tiles=1 << 20, chunk_ms=5.0,
                  device="cuda:0", screen=False, policy="aged", max_active_cells=1 << 25,
                  tile_cells=512, keep=None, solo=True, size_classes=(), solo_cells=None, half_pool=True,
-                 gather_ms=1.0):
+                 gather_ms=0.0):
         self.device = torch.device(device)
         self.budget = int(hbm_budget_bytes)
         if list(size_classes) != sorted(set(size_classes)) or any(c <= 0 for c in size_classes):
@@ -320,6 +319,16 @@ class Server:
         n = max(1, min(1024, int(self.chunk_ms / est_ms)))
         return n - n % spl if n >= spl else n
 
+    def _gather_until(self, queue, pending, active, now):
+        """When the queued jobs stop waiting for others (gather_ms after the
+        first one's arrival), or None once they do not: none is set, jobs run
+        already, the queue fills the members, no job is to come, or the time
+        has passed."""
+        if not self.gather_s or active or not queue or not pending or len(queue) >= self.max_members:
+            return None
+        end = min(s.arrival for s in queue) + self.gather_s
+        return end if now < end else None
+
     def run(self, trace) -> List[JobResult]:
         pending = collections.deque(sorted(trace, key=lambda s: s.arrival))
         queue = collections.deque()
@@ -339,9 +348,8 @@ class Server:
             # admission by HBM budget, member slots and the active-cells cap
             if len(queue) > 1:
                 queue = collections.deque(order_queue(queue, self.policy, now))
-            gather_end = min((s.arrival for s in queue), default=now) + self.gather_s
-            gather = not active and bool(pending) and len(queue) < self.max_members and now < gather_end
-            while queue and not gather:
+            gather = self._gather_until(queue, pending, active, now)
+            while queue and gather is None:
                 spec = queue[0]
                 need = footprint(spec)
                 if need > self.budget or (self.screen and not stability.stable(spec.relax)):
@@ -439,8 +447,8 @@ class Server:
                                          spec.storage, diag, status, **kept))
                 lat.close()
                 self.used -= need
-            if not active and pending and (gather or not queue):
-                wait = min(pending[0].arrival, gather_end if queue else math.inf) - (time.perf_counter() - t0)
+            if not active and pending and (gather is not None or not queue):
+                wait = min(pending[0].arrival, math.inf if gather is None else gather) - (time.perf_counter() - t0)
                 if wait > 0:
                     time.sleep(wait)
         return results

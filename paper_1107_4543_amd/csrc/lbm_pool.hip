@@ -74,12 +74,16 @@ struct lbm_pool {
     void *stage = nullptr;           // pinned host staging of the tables
     hipEvent_t ev_stage = nullptr;
     bool stage_pending = false;
-    bool dirty = true;
+    bool dirty = true;               // the unfinished members changed since plan()
+    bool stale = true;               // ... since the tables were built
     // One-step tiles are most of a table's entries and are needed only by
     // chunks with one-step launches: they join the tables with the first such
-    // chunk (256 lattices of 3e7 cells whose steps all end together: 2.7 ms of
-    // host time per lbm_pool_step with them, 0.8 without).
-    bool want_onestep = false, has_onestep = false;
+    // chunk and leave with the next change of members (256 lattices of 3e7
+    // cells whose steps all end together: 2.7 ms of host time per lbm_pool_step
+    // with them, 0.8 without).
+    bool has_onestep = false;
+    std::vector<int> chain;          // chain of each slot's member
+    int seg_rows = 0;                // rows of the strip tasks
     unsigned range_mask = 0;         // table ranges (class * kChains + chain) with tiles
     int ntiles = 0;
     unsigned two_mask = 0;           // table ranges with two-wave strip tasks
@@ -329,11 +333,51 @@ void drop_graphs(lbm_pool *P)
     P->graphs.clear();
 }
 
-// Rebuilds the member and tile tables on the host and uploads them.
-lbm_status upload(lbm_pool *P)
+// What the unfinished members ask of the tables and the launches: their chains,
+// strips or tiles, and the table ranges that hold members.
+void plan(lbm_pool *P)
 {
-    const bool onestep = P->want_onestep || P->shape.steps_per_launch < 2;
-    if (!P->dirty && (P->has_onestep || !onestep)) return LBM_OK;
+    if (!P->dirty) return;
+    // Chains: the unfinished members of each class, largest first, each to
+    // the chain of that class with the fewest cells so far.
+    P->chain.assign(P->max_members, 0);
+    std::vector<std::pair<int64_t, int>> by_size;
+    for (int i = 0; i < P->max_members; ++i) {
+        const Slot &sl = P->slots[i];
+        if (sl.lat && sl.t_done < sl.t_target) by_size.push_back({-(int64_t)sl.lat->v.nx * sl.lat->v.ny, i});
+    }
+    std::sort(by_size.begin(), by_size.end());
+    int64_t load[lbm::kClasses][lbm::kChains] = {};
+    for (const auto &e : by_size) {
+        const int c = class_of(P->slots[e.second].lat);
+        int best = 0;
+        for (int k = 1; k < lbm::kChains; ++k)
+            if (load[c][k] < load[c][best]) best = k;
+        P->chain[e.second] = best;
+        load[c][best] -= e.first;
+    }
+    P->tile = table_tile(P);
+    P->seg_rows = table_seg_rows(P);
+    static_assert(lbm::kRanges <= 32, "range mask bits");
+    P->range_mask = P->two_mask = 0;
+    const bool strips = !P->tile.steps && P->shape.steps_per_launch > 1 && wg_table(P->shape);
+    for (const auto &e : by_size) {
+        const lbm_lattice *L = P->slots[e.second].lat;
+        const unsigned bit = 1u << (class_of(L) * lbm::kChains + P->chain[e.second]);
+        P->range_mask |= bit;
+        if (strips && wg_strips(P->shape, L).two) P->two_mask |= bit;
+    }
+    P->dirty = false;
+    P->stale = true;
+}
+
+// Rebuilds the member and tile tables on the host and uploads them, with
+// one-step tiles where the next launches need them.
+lbm_status upload(lbm_pool *P, bool onestep)
+{
+    plan(P);
+    onestep = onestep || P->shape.steps_per_launch < 2;
+    if (!P->stale && (P->has_onestep || !onestep)) return LBM_OK;
     hipError_t e;
     if (P->stage_pending) {
         if ((e = hipEventSynchronize(P->ev_stage)) != hipSuccess) return phip(e, "hipEventSynchronize");
@@ -344,32 +388,8 @@ lbm_status upload(lbm_pool *P)
     lbm::PoolMember *mem = (lbm::PoolMember *)(base + ((char *)P->d_mem - P->ws));
     lbm::PoolTile *tiles = (lbm::PoolTile *)(base + ((char *)P->d_tiles - P->ws));
     memset(base, 0, (size_t)((char *)P->d_tiles - P->ws));
-    // Chains: the unfinished members of each class, largest first, each to
-    // the chain of that class with the fewest cells so far.
-    std::vector<int> chain(P->max_members, 0);
-    {
-        std::vector<std::pair<int64_t, int>> by_size;
-        for (int i = 0; i < P->max_members; ++i) {
-            const Slot &sl = P->slots[i];
-            if (sl.lat && sl.t_done < sl.t_target) by_size.push_back({-(int64_t)sl.lat->v.nx * sl.lat->v.ny, i});
-        }
-        std::sort(by_size.begin(), by_size.end());
-        int64_t load[lbm::kClasses][lbm::kChains] = {};
-        for (const auto &e : by_size) {
-            const int c = class_of(P->slots[e.second].lat);
-            int best = 0;
-            for (int k = 1; k < lbm::kChains; ++k)
-                if (load[c][k] < load[c][best]) best = k;
-            chain[e.second] = best;
-            load[c][best] -= e.first;
-        }
-    }
-    P->tile = table_tile(P);
-    const int seg_rows = table_seg_rows(P);
     struct T { int range; int64_t cells; lbm::PoolTile t; };
     std::vector<T> all, tasks, twos;
-    static_assert(lbm::kRanges <= 32, "range mask bits");
-    unsigned mask = 0;
     for (int i = 0; i < P->max_members; ++i) {
         const Slot &s = P->slots[i];
         lbm::PoolMember &m = mem[i];
@@ -394,12 +414,12 @@ lbm_status upload(lbm_pool *P)
         m.inv_scale = (float)L->v.inv_scale;
         m.cls = class_of(L);
         if (s.t_done >= s.t_target) continue;        // finished: no tiles
-        mask |= 1u << (m.cls * lbm::kChains + chain[i]);
+        const int range = m.cls * lbm::kChains + P->chain[i];
         const int r = tile_rows(P->shape, L), cw = tile_cols(P->shape, L);
         for (int y0 = 0; onestep && y0 < L->v.ny; y0 += r)
             for (int x0 = 0; x0 < L->v.nx; x0 += cw) {
                 T t{};
-                t.range = m.cls * lbm::kChains + chain[i];
+                t.range = range;
                 t.t.member = i;
                 t.t.y0 = y0;
                 t.t.x0 = x0;
@@ -417,7 +437,7 @@ lbm_status upload(lbm_pool *P)
                 const int y0 = (int)((int64_t)L->v.ny * sg / k), y1 = (int)((int64_t)L->v.ny * (sg + 1) / k);
                 for (int x0 = 0; x0 < L->v.nx; x0 += oc) {
                     T t{};
-                    t.range = m.cls * lbm::kChains + chain[i];
+                    t.range = range;
                     t.t.member = i;
                     t.t.y0 = y0;
                     t.t.x0 = x0;
@@ -430,13 +450,13 @@ lbm_status upload(lbm_pool *P)
             // four-wave (or one-wave) strips, then a two-wave one
             const bool wg = wg_table(P->shape);
             const WgStrips g = wg ? wg_strips(P->shape, L) : WgStrips{0, 0, 0};
-            const int w = task_cols(P->shape, L), k = segments_of(seg_rows, L);
+            const int w = task_cols(P->shape, L), k = segments_of(P->seg_rows, L);
             const int nfull = wg ? g.n4 : (L->v.nx + w - 1) / w;
             for (int sg = 0; sg < k; ++sg) {
                 const int y0 = (int)((int64_t)L->v.ny * sg / k), y1 = (int)((int64_t)L->v.ny * (sg + 1) / k);
                 for (int q = 0; q < nfull + g.two; ++q) {
                     T t{};
-                    t.range = m.cls * lbm::kChains + chain[i];
+                    t.range = range;
                     t.t.member = i;
                     t.t.y0 = y0;
                     t.t.x0 = q * w;
@@ -499,10 +519,8 @@ lbm_status upload(lbm_pool *P)
         return phip(e, "hipMemcpyAsync (pool tables)");
     if ((e = hipEventRecord(P->ev_stage, P->stream)) != hipSuccess) return phip(e, "hipEventRecord");
     P->stage_pending = true;
-    P->range_mask = mask;
-    P->two_mask = hmask;
     P->has_onestep = onestep;
-    P->dirty = false;
+    P->stale = false;
     return LBM_OK;
 }
 
@@ -550,7 +568,8 @@ int two_grid(const lbm_pool *P)
 // per T-step launch (chunk_steps).
 lbm_status get_graph(lbm_pool *P, unsigned mask, unsigned two, int len, int T, int nsingle, hipGraphExec_t *out)
 {
-    const int grid = launch_grid(P), mgrid = multi_grid(P), tgrid = two_grid(P);
+    // the one-step grid tells only loops with one-step launches apart
+    const int grid = nsingle ? launch_grid(P) : 0, mgrid = multi_grid(P), tgrid = two_grid(P);
     auto key = std::make_tuple(mask, two, len, T, nsingle, grid, mgrid, tgrid, P->tile.rows, P->tile.waves);
     auto it = P->graphs.find(key);
     if (it != P->graphs.end()) {
@@ -653,6 +672,7 @@ lbm_status run_chunk(lbm_pool *P, int kk)
 {
     hipError_t e;
     hipGraphExec_t ex;
+    plan(P);
     const int T = chunk_steps(P, kk);
     int64_t need = 0;
     for (const Slot &s : P->slots) {
@@ -661,11 +681,8 @@ lbm_status run_chunk(lbm_pool *P, int kk)
         need = std::max(need, std::min<int64_t>(rem, kk) - lbm::member_multi(rem, kk, T) * T);
     }
     need = std::min<int64_t>(need, lbm::chunk_single_launches(kk, T));
-    lbm_status st;
-    if (need > 0 && !P->has_onestep) {
-        P->want_onestep = true;
-        if ((st = upload(P)) != LBM_OK) return st;
-    }
+    lbm_status st = upload(P, need > 0);
+    if (st != LBM_OK) return st;
     st = get_graph(P, P->range_mask, P->two_mask, kk, T, (int)need, &ex);
     if (st != LBM_OK) return st;
     if ((e = hipGraphLaunch(ex, P->stream)) != hipSuccess) return phip(e, "hipGraphLaunch");
@@ -854,8 +871,6 @@ lbm_status lbm_pool_step(lbm_pool *pool, int64_t nsteps)
         for (const Slot &s : pool->slots)
             if (s.lat && !s.finishing) max_rem = std::max(max_rem, s.t_target - s.t_done);
         if (max_rem == 0) break;
-        lbm_status st = upload(pool);
-        if (st != LBM_OK) return st;
         // the longest recorded loop that fits: T 2^m steps (only T-step
         // launches for members that stay); below T, the rest in one chunk
         // (one shorter pass, see chunk_steps); one step per launch: powers
@@ -871,7 +886,8 @@ lbm_status lbm_pool_step(lbm_pool *pool, int64_t nsteps)
         } else {
             while ((int64_t)kk * 2 <= lim) kk *= 2;
         }
-        if ((st = run_chunk(pool, kk)) != LBM_OK) return st;
+        const lbm_status st = run_chunk(pool, kk);
+        if (st != LBM_OK) return st;
         nsteps -= kk;
         // finished members keep their (now idle) tiles until the next upload
         for (const Slot &s : pool->slots)
@@ -955,7 +971,7 @@ lbm_status lbm_pool_set_shape(lbm_pool *pool, const lbm_pool_shape *shape)
 lbm_status lbm_pool_time_launches(lbm_pool *pool, int32_t reps, double *avg_us)
 {
     if (!pool || reps < 1 || !avg_us) return pfail(LBM_E_INVAL, "bad argument");
-    lbm_status st = upload(pool);
+    lbm_status st = upload(pool, false);
     if (st != LBM_OK) return st;
     hipEvent_t e0, e1;
     hipError_t e;

@@ -409,11 +409,12 @@ TileShape tile_shape(const View &v)
 }
 
 // The same for T-step launches of several lattices together, at the T given;
-// *us: the launch's time by the model.
+// *us: the launch's time by the model, infinite where there is no shape (a
+// lattice beyond the reach of a buffer resource among them).
 TileShape tile_shape(const std::vector<const View *> &vs, int T, double *us_out)
 {
     TileShape best{0, 0, 0};
-    double best_us = INFINITY;
+    double best_us = *us_out = INFINITY;
     int storage = LBM_STORE_BF16;                         // the widest present
     for (const View *v : vs) {
         if (!tile_fits(*v)) return best;

@@ -535,16 +535,15 @@ int launch_grid(const lbm_pool *P)
 
 // Workgroups of a T-step launch: enough waves (workgroups, in a shared-halo
 // table) for the largest range's tasks, rounded up to a power of two, at
-// most the shape's grid.
+// most the shape's grid; register tiles are short and take a workgroup
+// each, whatever the grid (max_tiles is at most 2^26).
 int multi_grid(const lbm_pool *P)
 {
     const int per = wg_table(P->shape) ? 1 : P->shape.waves;
     const int need = (P->max_range_tasks + per - 1) / per;
-    // tiles are short: a workgroup each, whatever the shape's grid
-    const int most = P->tile.steps ? 1 << 20 : P->shape.grid;
     int g = 1;
-    while (g < need && g < most) g *= 2;
-    return std::min(g, most);
+    while (g < need && (P->tile.steps || g < P->shape.grid)) g *= 2;
+    return P->tile.steps ? g : std::min(g, P->shape.grid);
 }
 
 // Workgroups of a two-wave launch: one per task of the largest range,

@@ -43,15 +43,7 @@ struct TileArgs {
     float scale, inv_scale;
 };
 
-// Most waves per workgroup that the registers of R rows per lane leave room for
-// (512 registers per SIMD lane: a wave of the largest workgroup may hold
-// 2048 / waves of them).
-template <typename S, int R>
-constexpr int tile_max_waves()
-{
-    return sizeof(typename Store<S>::wide) == 8 && R > 4 ? 8 : 16;
-}
-
+constexpr int kTileWaves = 16;    // most waves of a workgroup (a lane then has 128 registers)
 constexpr int kTileCols = 64;     // columns of a tile: one per lane
 constexpr int kTileXch = kTileCols + 2;   // columns of an exchange row
 
@@ -224,7 +216,7 @@ __device__ __forceinline__ void tile_pass(const void *src_, void *dst_, int nx, 
 }
 
 template <typename S, typename C, int R>
-__global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(TileArgs<C> a)
+__global__ void __launch_bounds__(64 * kTileWaves) k_step_tile(TileArgs<C> a)
 {
     extern __shared__ char lds[];
     const int bid = remap_xcd((int)blockIdx.x, a.nblocks);
@@ -234,30 +226,25 @@ __global__ void __launch_bounds__((64 * tile_max_waves<S, R>())) k_step_tile(Til
                        min(a.out_rows, a.ny - y0), a.out_cols, lds);
 }
 
-// k_pool_multi's launch j on tile tasks.  A workgroup per tile where the grid
-// has as many, in contiguous ranges per XCD: neighbouring tiles' halos then
-// meet in one L2 (FP64, 60 members of 8.5M cells: 57.8 -> 53.8 us per step
-// against tiles dealt out in turn to 4096 workgroups; FP32, 256 of 30M: 122 ->
-// 102).
+// k_pool_multi's launch j on tile tasks: a workgroup per tile, in contiguous
+// ranges per XCD, so that neighbouring tiles' halos meet in one L2 (FP64, 60
+// members of 8.5M cells: 57.8 -> 53.8 us per step against tiles dealt out in turn
+// to 4096 workgroups; FP32, 256 of 30M: 122 -> 102).  The grid covers the
+// largest range; the workgroups beyond a range's own tiles end at once.
 template <typename S, typename C, int R>
-__global__ void __launch_bounds__((64 * tile_max_waves<S, R>()))
+__global__ void __launch_bounds__(64 * kTileWaves)
 k_pool_tile(const PoolHeader *__restrict__ hdr, const PoolMember *__restrict__ mem, const PoolTile *__restrict__ tiles,
             int range, int j, int T)
 {
     extern __shared__ char lds[];
-    const int begin = hdr->mbegin[range], end = hdr->mend[range];
-    for (int v = (int)blockIdx.x; v < end - begin; v += (int)gridDim.x) {
-        const int ti = begin + ((int)gridDim.x >= end - begin ? remap_xcd(v, end - begin) : v);
-        const PoolTile tile = tiles[ti];                 // workgroup-uniform
-        const PoolMember *m = mem + tile.member;
-        if ((int64_t)(j + 1) * T > m->t_target - m->t_done) continue;
-        const int par = (int)((m->cur0 + m->flips + j) & 1);
-        tile_pass<S, C, R>(m->buf[par], (void *)m->buf[par ^ 1], m->nx, m->ny, m->pitch, m->plane, member_relax<C>(m),
-                           m->scale, m->inv_scale, T, tile.x0, tile.y0, tile.nrows, tile.ncols, lds);
-        // every wave's reads of this tile's last exchange end before any
-        // wave writes the next tile's
-        __syncthreads();
-    }
+    const int begin = hdr->mbegin[range], n = hdr->mend[range] - begin;
+    if ((int)blockIdx.x >= n) return;
+    const PoolTile tile = tiles[begin + remap_xcd((int)blockIdx.x, n)];   // workgroup-uniform
+    const PoolMember *m = mem + tile.member;
+    if ((int64_t)(j + 1) * T > m->t_target - m->t_done) return;
+    const int par = (int)((m->cur0 + m->flips + j) & 1);
+    tile_pass<S, C, R>(m->buf[par], (void *)m->buf[par ^ 1], m->nx, m->ny, m->pitch, m->plane, member_relax<C>(m),
+                       m->scale, m->inv_scale, T, tile.x0, tile.y0, tile.nrows, tile.ncols, lds);
 }
 
 template <typename S, typename C>
@@ -287,7 +274,7 @@ hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const Ti
     a.inv_scale = (float)v.inv_scale;
     a.T = steps;
     tile_output({t.rows, t.waves, steps}, &a.out_cols, &a.out_rows);
-    if (steps < 1 || a.out_cols < 1 || a.out_rows < 1 || !tile_fits(v)) return hipErrorInvalidValue;
+    if (steps < 1 || a.out_cols < 1 || a.out_rows < 1 || t.waves > kTileWaves || !tile_fits(v)) return hipErrorInvalidValue;
     a.tiles_x = (v.nx + a.out_cols - 1) / a.out_cols;
     a.nblocks = a.tiles_x * ((v.ny + a.out_rows - 1) / a.out_rows);
     const uint64_t inv = (((uint64_t)1 << 32) + a.tiles_x - 1) / a.tiles_x;
@@ -297,7 +284,6 @@ hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const Ti
     const size_t lds = tile_lds(waves, sizeof(typename Store<S>::wide));
 #define LBM_TILE(R_)                                                                                      \
     case R_:                                                                                              \
-        if (waves > tile_max_waves<S, R_>()) return hipErrorInvalidValue;                                 \
         hipLaunchKernelGGL((k_step_tile<S, C, R_>), grid, block, lds, st, a);                             \
         break;
     switch (t.rows) {

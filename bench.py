@@ -72,6 +72,16 @@ def alg_ops_per_lu(storage, compute):
 
 
 ALU_PEAK = {"f32": 256 * 4 * 16 * 2.4e9, "f64": 256 * 4 * 16 * 2.4e9 / 2}
+# What the vector ALUs reach at most: a SIMD starts a 64-lane FP32 operation
+# every two cycles when its operands are vector registers or inline constants
+# (2.3-2.6 measured at two and more waves per SIMD; 4.2-4.5 with a
+# scalar-register operand), an FP64 operation every four (4.3-4.5 measured).
+# Twice ALU_PEAK either way; the roofline objects carry both.
+FULL_RATE = {"f32": 256 * 4 * 32 * 2.4e9, "f64": 256 * 4 * 16 * 2.4e9}
+
+
+def full_rate(compute, ops_per_s):
+    return {"peak": round(FULL_RATE[compute] / 1e12, 2), "frac": round(ops_per_s / FULL_RATE[compute], 4)}
 
 
 def read_profile(workload, storage, launch):
@@ -246,7 +256,7 @@ def pool_roofline(T, cells, launches, ms, traffic=None, steps=None):
     tops = ops / (ms * 1e-3) / 1e12
     peak = ALU_PEAK["f32"] / 1e12
     return dict({"bound": "alu", "achieved": round(tops, 2), "peak": round(peak, 2), "unit": "T F32 ops/s",
-                 "frac": round(tops / peak, 4), "traffic": traffic,
+                 "frac": round(tops / peak, 4), "full_rate": full_rate("f32", tops * 1e12), "traffic": traffic,
                  "algorithmic_ops_per_launch": round(ops / launches), "algorithmic_ops_timed": ops,
                  "ops_per_update": ops_lu, "hbm": hbm}, **common)
 
@@ -689,6 +699,7 @@ def main():
                           "population once for spl steps) over its average launch duration"}
         out["roofline"] = {"bound": "alu", "achieved": round(tops, 2), "peak": round(peak, 2),
                            "unit": "T %s ops/s" % compute.upper(), "frac": round(tops / peak, 4),
+                           "full_rate": full_rate(compute, tops * 1e12),
                            "traffic": traffic, "algorithmic_ops_per_launch": ops,
                            "ops_per_update": ops_lu,
                            "kernel": "k_step_multi (%d steps per pass)" % spl, "steps_per_launch": spl,

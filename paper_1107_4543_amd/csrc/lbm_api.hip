@@ -164,11 +164,12 @@ lbm_launch default_launch(const View &v)
 }
 
 // Register tiles in place of the default launch shape up to kTileCells cells,
-// by storage type.  Measured (us per step, strips -> tiles, a pulse on a field
-// at rest): FP32 1200 x 1000 6.6 -> 4.5, 2048^2 14.4 -> 12.6, 2600 x 2400 19.3 ->
-// 18.6; FP16 1500 x 1400 8.7 -> 7.2, 2048^2 14.0 -> 12.6, 2200 x 2150 13.7 -> 14.5;
-// BF16 2048^2 15.2 -> 13.0, 2300 x 2200 16.4 -> 15.3, 2400 x 2300 17.0 -> 17.1;
-// FP64 2048 x 1500 19.5 -> 17.9, 2048^2 25.4 -> 25.5, 2600 x 2400 35.2 -> 39.2.
+// by storage type: about where the two cross (us per step, strips -> tiles of the
+// model's choice, a pulse on a field at rest; profiles/k_step_tile_shapes.csv):
+// FP32 1200 x 1000 6.3 -> 4.4, 2048^2 14.5 -> 13.3, 2600 x 2400 19.2 -> 18.6; FP16
+// 1500 x 1400 8.8 -> 7.0, 2048^2 13.2 -> 12.5, 2200 x 2150 13.8 -> 14.6; BF16 2048^2
+// 14.7 -> 13.1, 2300 x 2200 16.5 -> 15.5, 2400 x 2300 17.1 -> 17.3; FP64 2048 x 1500
+// 20.0 -> 19.7, 2048^2 26.1 -> 27.2, 2600 x 2400 35.1 -> 39.7.
 // (The clock follows the power that the data cost: with noise in every cell
 // the strips, which move more through LDS and HBM, lose 15 %, the tiles 8 %.)
 constexpr int64_t kTileCells[4] = {(int64_t)7 << 19, (int64_t)3 << 21, (int64_t)1 << 22, (int64_t)5 << 20};

@@ -266,8 +266,9 @@ int table_seg_rows(const lbm_pool *P)
 
 // Time of a T-step launch of the unfinished members on shared-halo strips, by
 // the work it holds: rows of 256 lanes, T-1 start-up rows' worth for every
-// segment, at the rate the strips ran at on 12 sets of members per storage type
-// (one 64^2 to 256 of 64-1024 and two of 3000^2; lane-updates per us): less while
+// segment, at the rate that strips run at (lane-updates per us, from runs like
+// those of profiles/k_pool_tile_sets.txt, against which the time is 5-10 % low
+// where the device is full): less while
 // the tasks fill one round of workgroups, more once a second round fills
 // the gaps the first leaves.  Few tasks: the rows follow one another.
 double strip_launch_us(const lbm_pool *P)
@@ -293,13 +294,14 @@ double strip_launch_us(const lbm_pool *P)
 
 // Register tiles in place of strips for the unfinished members, or none: with
 // the shared-halo flags, where the tiles' launch takes less time by the two
-// models (their choice is the faster one in 35 of those 36 sets, 1-3 % off in
-// the other), while the tile table has room for them.  Measured, us per step,
-// strips -> tiles of the same T: FP32 one 64^2 4.4 -> 0.82, 40 of 64-200 (0.55M
-// cells) 6.9 -> 3.3, 20 of 64-1024 (3.2M) 14.3 -> 10.7, 120 of them (11.6M) 49.5
-// -> 38.1, 256 (30M) 89.9 -> 102.5, four 1500^2 29.3 -> 28.9, two 3000^2 51.9 ->
-// 59.9; FP64 20 of 64-1024 24.5 -> 20.5, 120 of them 94.6 -> 73.9; FP16 40 of
-// 64-200 7.0 -> 3.6, 60 of 64-1024 27.1 -> 28.6.
+// models, while the tile table has room for them.  In profiles/k_pool_tile_sets.txt
+// (12 sets per storage type) their choice is the faster one in 44 of 48 cases, and
+// costs 1 % (FP32, four of 1500^2), 2 and 11 % (FP64, 256 members and two of 3000^2)
+// and 7 % (FP16, 60 members) in the others.  Us per step, strips -> tiles of the
+// same T: FP32 one 64^2 4.4 -> 0.82, 40 of 64-200 (0.55M cells) 7.1 -> 3.3, 20 of
+// 64-1024 (3.2M) 14.4 -> 10.9, 120 of them (11.6M) 49.1 -> 38.5, 256 (30M) 91.3 ->
+// 102.9, two 3000^2 51.3 -> 60.2; FP64 20 of 64-1024 24.8 -> 20.2, 120 of them
+// 94.4 -> 73.2; FP16 40 of 64-200 7.4 -> 3.6, 256 of 64-1024 85.4 -> 91.3.
 lbm::TileShape table_tile(const lbm_pool *P)
 {
     const lbm_pool_shape &sh = P->shape;

@@ -17,10 +17,11 @@
 // vector ALUs fill; from there on it issues close to the ALU's rate, and what
 // bounds it is the share of the tile that is halo: a 64 x 48 tile
 // writes 52 x 36 cells after T = 7 steps.  Measured against what these sizes
-// took before (us per step): FP32 64^2 2.8 -> 0.71, 181 x 147 2.9 -> 0.80
-// (both one-step launches), 600 x 430 4.5 -> 1.5, 1000 x 760 5.9 -> 3.1, 2048^2
-// 17.1 -> 13.4 (strips); FP64 64^2 3.2 -> 0.92, 1500 x 1001 14.0 -> 9.8; BF16
-// 600 x 430 3.9 -> 1.6.
+// took before (us per step of step(n), a pulse on a field at rest;
+// profiles/k_step_tile_shapes.csv): FP32 64^2 3.7 -> 0.70, 181 x 147 3.7 -> 0.79,
+// 600 x 430 4.3 -> 1.5 (one-step launches), 1000 x 760 5.4 -> 3.0, 2048^2 14.5 ->
+// 13.4 (strips); FP64 64^2 3.7 -> 0.89, 1500 x 1001 11.5 -> 9.5; BF16 600 x 430
+// 3.9 -> 1.6.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -294,12 +295,14 @@ hipError_t launch_tile_typed(const View &v, const void *src, void *dst, const Ti
     return hipGetLastError();
 }
 
-// Launch time of a tile shape, from measurements of about 17 sizes from 37 x
-// 29 to 2600 x 2400 per storage type (6,000 launches each, residual 4 %; the
-// shape it picks is within 2-3 % of the best one on average).  The 16-bit rows
-// are 16 % below that fit, by what skipping single rows saved since (FP16 2048^2
-// then takes six steps per launch, 12.7 us per step, in place of four, 13.7;
-// pools of 120 lattices of 64^2 to 1024^2 tiles, 37.2, in place of strips, 39.5).
+// Launch time of a tile shape: a model fitted by storage type to a sweep of
+// sizes and shapes; the 16-bit rows are then set 16 % below their fit, by what
+// skipping single rows saves.  Against profiles/k_step_tile_shapes.csv (20 sizes
+// per storage type, every shape and T) the time of the shape that it picks is
+// 5 % (FP64), 6 % (FP32), 8 % (FP16, 6 % of it too low) and 13 % (BF16, 11 % too
+// low) off in the root mean square, and the pick takes 7, 3, 2 and 4 % longer than
+// the best shape on average, at most 23 % (FP64 2200 x 2150: six steps for eight),
+// 16, 12 and 13 %.
 // t0: launch and memory latency; row: one row of one wave, one step, on a SIMD
 // of its own; wg: load and store of one workgroup; bw: bytes per us to and from
 // memory.
@@ -351,14 +354,13 @@ double tile_us(int storage, const TileShape &t, const TileLoad &l)
            (m < 2 && n > 1 ? 0.5 * mem : 0.15 * std::min(issue, mem));
 }
 
-// The tile shapes in use hold the best one at 16 of 17 sizes of each storage
-// type: more than four rows per lane leave too few waves in flight, fewer than
-// twelve waves too little tile for its halo.  Four rows: FP64 with eight waves
-// (with sixteen, one workgroup per compute unit is left), 16-bit with sixteen
-// (61-63 registers: two workgroups per compute unit; a pool of eight FP16
-// lattices of 128^2 to 1024^2 11.2 -> 9.0 us per step against three rows).
-// FP32 with four rows and sixteen waves is 7 % slower at 2048^2 and within 2 %
-// below.
+// The tile shapes in use.  More than four rows per lane leave too few waves in
+// flight, fewer than twelve waves too little tile for its halo.  Four rows: FP64
+// with eight waves (with sixteen, one workgroup per compute unit is left), 16-bit
+// with sixteen (61-63 registers: two workgroups per compute unit; a pool of eight
+// FP16 lattices of 128^2 to 1024^2 11.2 -> 9.0 us per step against three rows).  FP32
+// not: sixteen waves of four rows against three take 3.76 | 3.01 us per step at
+// 1000 x 760, 5.47 | 5.38 at 1536 x 1024, 12.59 | 12.69 at 2048^2.
 constexpr int32_t kTileShapes[][2] = {{1, 12}, {1, 16}, {2, 12}, {2, 16}, {3, 12}, {3, 16}, {4, 8}, {4, 16}};
 bool tile_shape_used(int storage, const int32_t s[2])
 {

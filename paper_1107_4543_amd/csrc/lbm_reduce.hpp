@@ -39,19 +39,20 @@ struct RedShape {
     constexpr int blocks() const { return bx * by; }
 };
 
+// (In unsigned 32 bits, which hold nx and a stretch of columns beside it: 64-bit
+// divisions cost a host-bound projection 0.1 us of 8.)
 constexpr RedShape red_shape(int32_t nx, int32_t ny, int threads, int max_blocks)
 {
     RedShape g{};
     while ((1 << g.shift) < threads && (1 << g.shift) < nx) ++g.shift;
-    const int64_t w = 1 << g.shift, h = threads >> g.shift;
-    const int64_t tx = (nx + w - 1) / w;
-    const int64_t cols = w * ((tx + max_blocks - 1) / max_blocks);
-    g.cols = (int32_t)cols;
-    g.bx = (int32_t)((nx + cols - 1) / cols);
+    const uint32_t w = 1u << g.shift, h = (uint32_t)threads >> g.shift, most = (uint32_t)max_blocks;
+    const uint32_t tx = ((uint32_t)nx + w - 1) >> g.shift;
+    const uint32_t cols = w * ((tx + most - 1) / most), bx = ((uint32_t)nx + cols - 1) / cols;
     // at least two cells per thread
-    const int64_t most = max_blocks / g.bx, want = (ny + 2 * h - 1) / (2 * h);
-    g.by = (int32_t)(want < most ? want : most);
-    if (g.by < 1) g.by = 1;
+    const uint32_t want = ((uint32_t)ny + 2 * h - 1) / (2 * h), by = most / bx < want ? most / bx : want;
+    g.cols = (int32_t)cols;
+    g.bx = (int32_t)bx;
+    g.by = by > 1 ? (int32_t)by : 1;
     return g;
 }
 

@@ -227,7 +227,11 @@ LBM_API lbm_status lbm_init_equilibrium(lbm_lattice *lat, const double *rho, con
  * bit-identical results. */
 LBM_API lbm_status lbm_step(lbm_lattice *lat, int64_t n);
 /* Kernel launches lbm_step(lat, n) makes with the current shapes; -1 if
- * lat is NULL or n < 0. */
+ * lat is NULL or n < 0.  Each launch reads one of the lattice's two buffers and
+ * writes the other, so a captured lbm_step can be replayed on its own result
+ * only where this count is even; it depends on the launch shape and on the
+ * register tiles in use (lbm_set_launch fixes the former, lbm_set_tiles the
+ * latter). */
 LBM_API int64_t lbm_step_launches(const lbm_lattice *lat, int64_t n);
 
 /* Macroscopic fields of the current state (Sec. 2.1, Eq. q-macro):

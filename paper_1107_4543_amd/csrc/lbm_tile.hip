@@ -12,7 +12,7 @@
 //
 // Why tiles: below about 2^22 cells the strips of k_step_multi are too few to
 // fill the device with segments tall enough to pay for their 2 (T-1) start-up
-// rows, and one-step launches spend most of their 2.8 us on launch and memory
+// rows, and one-step launches spend most of their 2-4 us on launch and memory
 // latency.  A tile launch costs about 3.3 us plus 0.3 us per step until the
 // vector ALUs fill; from there on it issues close to the ALU's rate, and what
 // bounds it is the share of the tile that is halo: a 64 x 48 tile
